@@ -18,7 +18,7 @@
 #include "../../include/fgh.h"
 #include "fgh_internal.hpp"
 #include "fgh_launch.hpp"
-#include "fgh_v2.hpp"
+#include "fgh_gen.hpp"
 #include "fgh_batch.hpp"
 
 using namespace fgh;
@@ -47,9 +47,27 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 int ncoef_for(int d) { return d == 2 ? 3 : 6; }
 
+// The two-step split L = q p of the run-time-length passes.  Both factors are register radices where
+// that is possible: the pair nearest to equal, the larger one in step B as long as the middle
+// pass can hold two of its lines in registers.  Otherwise q is the largest register radix that
+// divides L, with a dense step of p = L / q points.
+void split_length(int L, Axis* ax)
+{
+    ax->q = 1;
+    ax->p = L;
+    for (int q = 1; q <= kGenRadix; q += 2) {
+        if (L % q) continue;
+        if (L / q <= kGenRadix && q > L / q) break;
+        ax->q = q;
+        ax->p = L / q;
+    }
+    if (ax->p <= kMidFusedRadix) std::swap(ax->q, ax->p);
+}
+
 // Radix sequence of an odd length: 7s, 5s, 3s, then any other prime factor.
 bool factorize(int L, Axis* ax)
 {
+    split_length(L, ax);
     int n = L, k = 0;
     const int small[3] = {7, 5, 3};
     for (int p : small)
@@ -73,6 +91,7 @@ struct Config {
     int rpb, npen, P_axis, P_mid;
     size_t lds_first, lds_first_v2, lds_last_v2, lds_axis, lds_mid;
     bool v2_row, v2_axis, v2_mid;
+    GenTile row, axis, mid;  // run-time-length passes (use_run_time_lengths; ok: chosen)
 };
 
 int env_int(const char* name, int dflt)
@@ -160,6 +179,29 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
     return c;
 }
 
+// The run-time-length passes for the axes without a specialised kernel, where a tile fits: they
+// index with 32 bits too, and a dense step is limited by the registers of a workgroup.  Lengths
+// whose smallest mixed-radix tile exceeds the LDS stay refused.
+//
+// They serve every double-precision application and fgh_apply_f32.  The single-precision loops of
+// refined solves keep the mixed-radix passes: the rounding of an inner solve enters a refined
+// result at about 1e-8 of it (the outer loop stops at the caller's tolerance), and those results
+// stay what they have been.
+void use_run_time_lengths(const Geo& g, size_t cs, size_t rs, Config* c)
+{
+    const int d = g.d;
+    const long long span = (long long)d * std::max(g.npts, std::max(g.s1, g.s2));
+    const size_t tabb = kMaxPhases * 6 * rs, max_lds = 160 * 1024;
+    auto fits = [&](int L, size_t lines) {
+        return span < (1LL << 31) && (L + lines * (size_t)L) * cs + tabb <= max_lds;
+    };
+    Axis ax[3];
+    for (int a = 0; a < d; a++) split_length(ax[a].L = g.L[a], &ax[a]);
+    if (!c->v2_row && fits(g.L[d - 1], 2 * (size_t)((d + 1) / 2))) c->row = gen_row_tile(ax[d - 1], d, g.rows, cs, env_int("FGH_RPB", 32));
+    if (d == 3 && !c->v2_axis && fits(g.L[1], 2)) c->axis = gen_axis_tile(ax[1], g.Hb, (long long)g.L[0] * d, cs);
+    if (!c->v2_mid && fits(g.L[0], (size_t)d + 1)) c->mid = gen_mid_tile(ax[0], g.cols_mid, cs);
+}
+
 bool make_geo(int d, const int32_t* N, int rule, Geo* g)
 {
     if (d != 2 && d != 3) return false;
@@ -217,11 +259,14 @@ Layout make_layout(const Geo& g, const int32_t* N, int rule, int prec, int akind
     if (v64 < (size_t)d * sp * 16) v64 = (size_t)d * sp * 16;
     l.vec64 = take(v64);
     l.vec32 = take(prec == FGH_FP32_REFINED ? (size_t)4 * nv * 4 : 0);
-    const Config c64 = choose_config(g, 16, 8);
-    const Config c32 = choose_config(g, 8, 4);
-    long long nb = (g.rows + c64.rpb - 1) / c64.rpb;
-    const long long nb32 = (g.rows + c32.rpb - 1) / c32.rpb;
-    if (nb32 > nb) nb = nb32;
+    // partial sums: one per block of the last pass, whichever row kernels a precision may use
+    long long nb = 0;
+    for (int f32 = 0; f32 < 2; f32++) {
+        Config c = choose_config(g, f32 ? 8 : 16, f32 ? 4 : 8);
+        nb = std::max(nb, (g.rows + c.rpb - 1) / c.rpb);
+        use_run_time_lengths(g, f32 ? 8 : 16, f32 ? 4 : 8, &c);
+        if (c.row.ok) nb = std::max(nb, (g.rows + c.row.n - 1) / c.row.n);
+    }
     long long np = nb;
     if (np < 1024 * 2 + 2) np = 1024 * 2 + 2;
     if (np < 512 * 18) np = 512 * 18;
@@ -406,9 +451,39 @@ void fill_opplan_at(OpPlan* op, const Geo& g, bool f32, char* const tw[3], char*
     op->v2_row = c.v2_row;
     op->v2_axis = c.v2_axis;
     op->v2_mid = c.v2_mid;
+    op->gen_row = op->gen_axis = op->gen_mid = false;
     op->partials = partials;
     op->sc = sc;
     op->stream = stream;
+}
+
+// Switches an operator description to the run-time-length passes where they apply.
+void set_run_time_lengths(OpPlan* op, bool f32)
+{
+    Config c = choose_config(op->g, f32 ? 8 : 16, f32 ? 4 : 8);
+    use_run_time_lengths(op->g, f32 ? 8 : 16, f32 ? 4 : 8, &c);
+    if (c.row.ok) {
+        op->gen_row = true;
+        op->rpb = op->rpb_first = op->rpb_first_x = op->rpb_fused = c.row.n;
+        op->npen = (c.row.n * op->g.d + 1) / 2;
+        op->lds_first = op->lds_first_v2 = op->lds_first_x = op->lds_last_v2 = op->lds_fused = c.row.lds;
+        op->th_row = c.row.threads;
+        op->ni_row = c.row.ni;
+    }
+    if (c.axis.ok) {
+        op->gen_axis = true;
+        op->P_axis = c.axis.n;
+        op->lds_axis = c.axis.lds;
+        op->th_axis = c.axis.threads;
+        op->ni_axis = c.axis.ni;
+    }
+    if (c.mid.ok) {
+        op->gen_mid = true;
+        op->P_mid = c.mid.n;
+        op->lds_mid = c.mid.lds;
+        op->th_mid = c.mid.threads;
+        op->ni_mid = c.mid.ni;
+    }
 }
 
 void fill_opplan(fgh_plan p, OpPlan* op, bool f32)
@@ -433,7 +508,7 @@ void tune_log(const char* pass, bool f32, int cand, int pad, float ms)
 // depend on the width, so results are identical whatever is chosen.
 fgh_status tune_axis(fgh_plan p, OpPlan* op, bool f32)
 {
-    if (p->d != 3 || env_int("FGH_TUNE", 1) == 0 || env_int("FGH_P_EXACT", 0) != 0) return FGH_OK;
+    if (p->d != 3 || op->gen_axis || env_int("FGH_TUNE", 1) == 0 || env_int("FGH_P_EXACT", 0) != 0) return FGH_OK;
     static std::mutex mu;
     static std::map<std::vector<long long>, int> cache;
     const Geo& g = op->g;
@@ -2135,6 +2210,7 @@ fgh_status fgh_plan_create(fgh_plan* out, int d, const int32_t* N, fgh_rule rule
             for (int q = 0; q < nc; q++)
                 if (!std::isfinite(p->tab[i][q])) return fail(FGH_E_NOT_SPD);
     fill_opplan(p, &p->op64, false);
+    set_run_time_lengths(&p->op64, false);
     fill_opplan(p, &p->op32, true);
     const long long nv = (long long)d * p->g.npts;
     double* v64 = reinterpret_cast<double*>(p->ws + p->lay.vec64);
@@ -2388,8 +2464,10 @@ fgh_status fgh_apply_f32(fgh_plan p, const float* x, float* y)
     a.epi = EPI_STORE;
     a.sgn = 1.0;
     a.y = y;
+    OpPlan op = p->op32;
+    set_run_time_lengths(&op, true);
     int nb = 0;
-    HIPOK(run_apply<float>(p->op32, a, &nb));
+    HIPOK(run_apply<float>(op, a, &nb));
     return FGH_OK;
 }
 
@@ -2434,6 +2512,7 @@ fgh_status fgh_apply_noalloc(int d, const int32_t* N, fgh_akind a_kind, const vo
     OpPlan op{};
     fill_opplan_at(&op, g, false, tw, base + l.SA, base + l.SB, reinterpret_cast<double*>(base + l.partials),
                    reinterpret_cast<Scalars*>(base + l.scalars), st);
+    set_run_time_lengths(&op, false);
     op.A = ca;
     ApplyArgs a;
     a.op = OP_AX;

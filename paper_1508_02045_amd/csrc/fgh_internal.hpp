@@ -29,6 +29,7 @@ struct Axis {
     int L;
     int nst;
     int rad[kMaxRadices];
+    int q, p;  // L = q p of the run-time-length passes: q <= 17, p <= 17 or a dense product
     int tw;  // offset (complex elements) of exp(-2 pi i m / L), m in [0, L), in the table buffer
 };
 

@@ -5,11 +5,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
-#include <mutex>
 #include <cstdlib>
 
 #include "fgh_args.hpp"
+#include "fgh_dispatch.hpp"
 #include "fgh_launch.hpp"
 #include "fgh_v2.hpp"
 
@@ -895,38 +894,6 @@ __global__ void k_real_part(long long n, const double2* __restrict__ c, double* 
 // ==========================================================================================
 __global__ void k_set_scalar(double* dst, double v) { *dst = v; }
 
-// Allow dynamic LDS above 64 KB for a kernel (gfx950 has 160 KB per compute unit).
-static hipError_t allow_lds(const void* fn, size_t bytes)
-{
-    if (bytes <= 65536) return hipSuccess;
-    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-// The attribute of each kernel only ever rises, so that no attribute call is made while a stream
-// is being captured into a graph once the largest size has been seen.  Raising is serialised per
-// kernel: the recorded size is stored only after the call has succeeded and only while holding the
-// kernel's lock, so concurrent launches from several threads (server workers, plan-time tuning)
-// can neither lower the attribute nor record a size the attribute does not allow.
-#define LAUNCH_LDS(KERNEL, GRID, LDS, STREAM, ...)                                              \
-    do {                                                                                        \
-        static std::atomic<size_t> lds_set_{65536};                                            \
-        static std::mutex lds_mu_;                                                              \
-        if ((LDS) > lds_set_.load(std::memory_order_acquire)) {                                 \
-            std::lock_guard<std::mutex> lds_lk_(lds_mu_);                                       \
-            if ((LDS) > lds_set_.load(std::memory_order_relaxed)) {                             \
-                hipError_t e_ = allow_lds(reinterpret_cast<const void*>(&KERNEL), (LDS));       \
-                if (e_ != hipSuccess) return e_;                                                \
-                lds_set_.store((LDS), std::memory_order_release);                               \
-            }                                                                                   \
-        }                                                                                       \
-        if (g_pass_events.start) {                                                              \
-            const PassEvents pe_ = g_pass_events;                                               \
-            g_pass_events = PassEvents{};                                                       \
-            hipExtLaunchKernelGGL(KERNEL, GRID, dim3(kThreads), (LDS), (STREAM), pe_.start, pe_.stop, 0, \
-                                  __VA_ARGS__);                                                 \
-        } else {                                                                                \
-            hipLaunchKernelGGL(KERNEL, GRID, dim3(kThreads), (LDS), (STREAM), __VA_ARGS__);      \
-        }                                                                                       \
-    } while (0)
 static inline unsigned grid_for(long long n, int per = kThreads, int cap = 4096)
 {
     long long b = (n + per - 1) / per;
@@ -1053,6 +1020,7 @@ static hipError_t launch_last_ak(const OpPlan& op, const LastArgs<T>& la, int ep
 template <typename T, int D>
 static hipError_t launch_first(const OpPlan& op, const FirstArgs<T>& fa, int opc, unsigned nblk)
 {
+    if (op.gen_row) return gen_first<T>(op, fa, opc, nblk);
     switch (op.A.kind) {
         case AK_SYM: return launch_first_ak<T, D, AK_SYM>(op, fa, opc, nblk);
         case AK_ISO: return launch_first_ak<T, D, AK_ISO>(op, fa, opc, nblk);
@@ -1064,6 +1032,7 @@ static hipError_t launch_first(const OpPlan& op, const FirstArgs<T>& fa, int opc
 template <typename T, int D>
 static hipError_t launch_last(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned nblk)
 {
+    if (op.gen_row) return gen_last<T>(op, la, epi, nblk);
     switch (op.A.kind) {
         case AK_SYM: return launch_last_ak<T, D, AK_SYM>(op, la, epi, nblk);
         case AK_ISO: return launch_last_ak<T, D, AK_ISO>(op, la, epi, nblk);
@@ -1075,6 +1044,7 @@ static hipError_t launch_last(const OpPlan& op, const LastArgs<T>& la, int epi, 
 template <typename T, int D>
 static hipError_t launch_middle(const OpPlan& op, const MidArgs<T>& ma, int mult)
 {
+    if (op.gen_mid) return gen_middle<T>(op, ma, mult);
     const size_t lds = op.lds_mid;
     if (mult == MULT_G)
         LAUNCH_LDS((k_middle<T, D, MULT_G>), dim3(ma.ntiles), lds, op.stream, ma);
@@ -1084,8 +1054,9 @@ static hipError_t launch_middle(const OpPlan& op, const MidArgs<T>& ma, int mult
 }
 
 template <typename T>
-static hipError_t launch_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer)
+static hipError_t launch_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer, int B)
 {
+    if (op.gen_axis) return gen_axis<T>(op, xa, inv, outer, B);
     dim3 grid(xa.ntiles, outer, op.g.d);
     if (inv)
         LAUNCH_LDS((k_axis<T, true>), grid, op.lds_axis, op.stream, xa);
@@ -1456,7 +1427,7 @@ static hipError_t apply_d(const OpPlan& op, const ApplyArgs& a, int* nblocks_las
     if (D == 3) {
         const bool prof_PK_AXIS_FWD = op.prof && op.prof->wants(PK_AXIS_FWD);
         if (prof_PK_AXIS_FWD && (e = op.prof->begin(PK_AXIS_FWD)) != hipSuccess) return e;
-        if ((e = op.v2_axis ? v2_axis<T>(op, bu.xf, false, g.L[0], g.B[1]) : launch_axis<T>(op, bu.xf, false, g.L[0])) !=
+        if ((e = op.v2_axis ? v2_axis<T>(op, bu.xf, false, g.L[0], g.B[1]) : launch_axis<T>(op, bu.xf, false, g.L[0], g.B[1])) !=
             hipSuccess)
             return e;
         if (prof_PK_AXIS_FWD && (e = op.prof->end()) != hipSuccess) return e;
@@ -1469,7 +1440,7 @@ static hipError_t apply_d(const OpPlan& op, const ApplyArgs& a, int* nblocks_las
     if (D == 3) {
         const bool prof_PK_AXIS_INV = op.prof && op.prof->wants(PK_AXIS_INV);
         if (prof_PK_AXIS_INV && (e = op.prof->begin(PK_AXIS_INV)) != hipSuccess) return e;
-        if ((e = op.v2_axis ? v2_axis<T>(op, bu.xi, true, g.L[0], g.B[1]) : launch_axis<T>(op, bu.xi, true, g.L[0])) !=
+        if ((e = op.v2_axis ? v2_axis<T>(op, bu.xi, true, g.L[0], g.B[1]) : launch_axis<T>(op, bu.xi, true, g.L[0], g.B[1])) !=
             hipSuccess)
             return e;
         if (prof_PK_AXIS_INV && (e = op.prof->end()) != hipSuccess) return e;
@@ -1519,7 +1490,7 @@ hipError_t run_axis_only(const OpPlan& op)
     xa.out = static_cast<cpx<T>*>(op.SB);
     xa.twg = static_cast<const cpx<T>*>(op.tw[1]);
     xa.done = nullptr;
-    return op.v2_axis ? v2_axis<T>(op, xa, false, g.L[0], g.B[1]) : launch_axis<T>(op, xa, false, g.L[0]);
+    return op.v2_axis ? v2_axis<T>(op, xa, false, g.L[0], g.B[1]) : launch_axis<T>(op, xa, false, g.L[0], g.B[1]);
 }
 template hipError_t run_axis_only<double>(const OpPlan&);
 template hipError_t run_axis_only<float>(const OpPlan&);
@@ -1610,8 +1581,19 @@ static hipError_t axis_custom(const OpPlan& op, const Axis& ax, const void* tw, 
     xa.bin = bin;
     xa.bout = bout;
     xa.inner = inner;
+    OpPlan o = op;
     int P = 16;
-    while (P > 1 && (size_t)(ax.L + 2 * P * ax.L) * 16 > 80 * 1024) P >>= 1;
+    const GenTile t = gen_axis_tile(ax, inner, (long long)outer * op.g.d, 16);
+    o.gen_axis = t.ok && op.g.d * std::max(in_cs, out_cs) < (1LL << 31);
+    if (o.gen_axis) {
+        P = t.n;
+        o.lds_axis = t.lds;
+        o.th_axis = t.threads;
+        o.ni_axis = t.ni;
+    } else {
+        while (P > 1 && (size_t)(ax.L + 2 * P * ax.L) * 16 > 80 * 1024) P >>= 1;
+        o.lds_axis = (size_t)(ax.L + 2 * P * ax.L) * 16;
+    }
     xa.P = P;
     xa.ntiles = (inner + P - 1) / P;
     xa.in_os = in_os;
@@ -1621,9 +1603,7 @@ static hipError_t axis_custom(const OpPlan& op, const Axis& ax, const void* tw, 
     xa.in = reinterpret_cast<const cpx<double>*>(in);
     xa.out = reinterpret_cast<cpx<double>*>(out);
     xa.twg = static_cast<const cpx<double>*>(tw);
-    OpPlan o = op;
-    o.lds_axis = (size_t)(ax.L + 2 * P * ax.L) * 16;
-    return launch_axis<double>(o, xa, inv, outer);
+    return launch_axis<double>(o, xa, inv, outer, bin ? nin : bout ? nout : ax.L);
 }
 
 hipError_t run_prolong(const OpPlan& opn, const OpPlan& opm, const double* xn, double* ym)

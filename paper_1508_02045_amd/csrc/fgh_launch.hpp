@@ -66,6 +66,10 @@ struct OpPlan {
     int rpb_fused;           // the fused last + first pass: rows per block (even or the last pass's; tuned)
     size_t lds_fused;        //   and its LDS (one row buffer, two coefficient tables)
     bool v2_row, v2_axis, v2_mid;  // size-specialised kernels for the row / axis-1 / axis-0 passes
+    // run-time lengths on the register / matrix-core passes (otherwise the mixed-radix ones), with
+    // their threads per workgroup and dense products per wavefront (0: both steps in registers)
+    bool gen_row, gen_axis, gen_mid;
+    int th_row, th_axis, th_mid, ni_row, ni_axis, ni_mid;
     double* partials;        // one double per block of the last pass (and of vector kernels)
     Scalars* sc;
     hipStream_t stream;
@@ -103,6 +107,26 @@ struct ApplyArgs {
     // the separate single-block reduction launch
     int defer_redop = -1;
 };
+
+// Tile of a run-time-length pass: rows per block or columns per tile, threads, dense products per
+// wavefront and LDS bytes; ok = false where the mixed-radix passes are used.
+struct GenTile {
+    bool ok;
+    int n, threads, ni;
+    size_t lds;
+};
+// cs: bytes per complex; rows / cols: the pass's extent; outer: independent blocks of columns
+GenTile gen_row_tile(const Axis& ax, int d, long long rows, size_t cs, int cap);  // cap: rows at most
+GenTile gen_axis_tile(const Axis& ax, int inner, long long outer, size_t cs);
+GenTile gen_mid_tile(const Axis& ax, int cols, size_t cs);
+template <typename T>
+hipError_t gen_first(const OpPlan& op, const FirstArgs<T>& fa, int opc, unsigned nblk);
+template <typename T>
+hipError_t gen_last(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned nblk);
+template <typename T>
+hipError_t gen_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer, int B);
+template <typename T>
+hipError_t gen_middle(const OpPlan& op, const MidArgs<T>& ma, int mult);
 
 // Whether the plan's last pass can run the next body's first pass (see ApplyArgs::next_op).
 inline bool fusable(const OpPlan& op) { return op.v2_row; }

@@ -122,20 +122,35 @@ __device__ __forceinline__ cpx<T> croot(int m)
 template <typename T, int R, bool INV>
 __device__ __forceinline__ void reg_dft(cpx<T>* v);
 
-// Direct DFT for a prime R > 7.
+// DFT of an odd prime R > 7 from the sums and differences of mirrored inputs: (R - 1)^2 / 4 real
+// factors on complex values for the cosine and the sine half each.
 template <typename T, int R, bool INV>
-__device__ __forceinline__ void dft_direct(cpx<T>* v)
+__device__ __forceinline__ void dft_prime(cpx<T>* v)
 {
-    cpx<T> out[R];
+    constexpr int H = (R - 1) / 2;
+    cpx<T> a[H], b[H], y0 = v[0];
+    const cpx<T> x0 = v[0];
 #pragma unroll
-    for (int k = 0; k < R; k++) {
-        cpx<T> acc = v[0];
-#pragma unroll
-        for (int n = 1; n < R; n++) acc = acc + cmul(v[n], croot<T, R, INV>(n * k));
-        out[k] = acc;
+    for (int m = 1; m <= H; m++) {
+        a[m - 1] = v[m] + v[R - m];
+        b[m - 1] = v[m] - v[R - m];
+        y0 = y0 + a[m - 1];
     }
+    v[0] = y0;
 #pragma unroll
-    for (int k = 0; k < R; k++) v[k] = out[k];
+    for (int k = 1; k <= H; k++) {
+        cpx<T> re = x0, im = {T(0), T(0)};
+#pragma unroll
+        for (int m = 1; m <= H; m++) {
+            const cpx<T> w = croot<T, R, false>(m * k);  // (cos, -sin)
+            re = re + w.x * a[m - 1];
+            im = im + w.y * b[m - 1];
+        }
+        // X_k = re + i im and X_{R-k} = re - i im with im = -sum sin b (forward; swapped inverse)
+        const cpx<T> p = {re.x - im.y, re.y + im.x}, q = {re.x + im.y, re.y - im.x};
+        v[k] = INV ? q : p;
+        v[R - k] = INV ? p : q;
+    }
 }
 
 template <typename T, int R, bool INV>
@@ -146,7 +161,7 @@ __device__ __forceinline__ void reg_dft(cpx<T>* v)
     } else if constexpr (R == 3 || R == 5 || R == 7) {
         dft_small<T, R, INV>(v);
     } else if constexpr (smallest_factor(R) == R) {
-        dft_direct<T, R, INV>(v);
+        dft_prime<T, R, INV>(v);
     } else {
         constexpr int R1 = smallest_factor(R);
         constexpr int R2 = R / R1;
@@ -236,11 +251,26 @@ constexpr int ku_for(int L)
     return k < 2 ? 2 : (k > 8 ? 8 : k);
 }
 
-// Stage 0 of the first pass for kU points starting at this thread's index base + threadIdx.x:
-// z = A(pt) u with u per FirstOp; writes the real rows Zr[(r D + c) L + i].
-template <typename T, int D, int L, int KU, bool IL = false, bool XD = false>
+// A row length: compile-time (LT > 0, the size-specialised kernels) or run-time (LT = 0), and the
+// row of a tile's point index.  The run-time form divides by multiplying with the reciprocal: the
+// error of (i + 0.5) / L stays below half of 1 / L for indices below 2^21, so the floor is exact.
+template <int LT>
+struct RowLen {
+    int l;
+    float inv;
+    __device__ __forceinline__ int len() const { return LT ? LT : l; }
+    __device__ __forceinline__ int row(int i) const
+    {
+        return LT ? i / (LT ? LT : 1) : (int)(((float)i + 0.5f) * inv);
+    }
+};
+
+// Stage 0 of the first pass for KU points starting at this thread's index base + threadIdx.x:
+// z = A(pt) u with u per FirstOp.  Real rows 2m and 2m + 1 of the tile (row r, component c:
+// r D + c) are written as the real and imaginary parts of complex row m (RS slots apart).
+template <typename T, int D, int LT, int KU, bool XD = false>
 __device__ __forceinline__ void first_stage0_chunk(const FirstArgs<T>& a, int op, const T* tab, T beta, int base,
-                                                   int total, int lim, long long pt0, T* Zr)
+                                                   int total, int lim, long long pt0, T* Zr, RowLen<LT> rl, int RS)
 {
     const unsigned npts = (unsigned)a.g.npts;  // 32-bit offsets: d |grid| < 2^31 here
     unsigned pt[KU];
@@ -339,23 +369,21 @@ __device__ __forceinline__ void first_stage0_chunk(const FirstArgs<T>& a, int op
     for (int u = 0; u < KU; u++) {
         const int idx = base + u * (int)blockDim.x + (int)threadIdx.x;
         if (idx < total) {
-            const int r = idx / L;
-            const int i = idx - r * L;
+            const int r = rl.row(idx);
+            const int i = idx - r * rl.len();
 #pragma unroll
             for (int c = 0; c < D; c++) {
                 const int q = r * D + c;
-                // IL: real rows 2m, 2m+1 interleaved as the real and imaginary parts of complex row m
-                const int at = IL ? ((q >> 1) * L + i) * 2 + (q & 1) : q * L + i;
-                Zr[at] = ok[u] ? z[u][c] : T(0);
+                Zr[((q >> 1) * RS + i) * 2 + (q & 1)] = ok[u] ? z[u][c] : T(0);
             }
         }
     }
 }
 
 // Epilogue of the last pass for kU points: y from the real rows Zr, the solver update per Epi.
-template <typename T, int D, int L, int epi, int KU>
-__device__ __forceinline__ double last_epilogue_chunk(const LastArgs<T>& a, const T* tabinv, int base,
-                                                      int total, int lim, long long pt0, const T* Zr)
+template <typename T, int D, int LT, int epi, int KU>
+__device__ __forceinline__ double last_epilogue_chunk(const LastArgs<T>& a, const T* tabinv, int base, int total,
+                                                      int lim, long long pt0, const T* Zr, RowLen<LT> rl, int RS)
 {
     const unsigned npts = (unsigned)a.g.npts;  // 32-bit offsets: d |grid| < 2^31 here
     unsigned pt[KU];
@@ -367,13 +395,13 @@ __device__ __forceinline__ double last_epilogue_chunk(const LastArgs<T>& a, cons
         ok[u] = idx < lim;
         pt[u] = ok[u] ? (unsigned)(pt0 + idx) : 0u;
         const int ii = ok[u] ? idx : 0;
-        const int r = ii / L;
-        const int i = ii - r * L;
+        const int r = rl.row(ii);
+        const int i = ii - r * rl.len();
 #pragma unroll
         for (int c = 0; c < D; c++) {
-            // real rows 2m, 2m+1 are the real and imaginary parts of packed row m (stride L + 1)
+            // real rows 2m, 2m+1 are the real and imaginary parts of packed row m (RS slots apart)
             const int q = r * D + c;
-            y[u][c] = Zr[((q >> 1) * (L + 1) + i) * 2 + (q & 1)];
+            y[u][c] = Zr[((q >> 1) * RS + i) * 2 + (q & 1)];
         }
     }
     double acc = 0.0;
@@ -656,12 +684,12 @@ __device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, long l
         const int lim = left < total ? (int)left : total;
         if (op == OP_AP_CG && a.xd) {
             for (int base = 0; base < total; base += KX * blockDim.x)
-                first_stage0_chunk<T, D, L, KX, true, true>(a, op, tab, beta, base, total, lim, pt0,
-                                                            reinterpret_cast<T*>(Zc));
+                first_stage0_chunk<T, D, L, KX, true>(a, op, tab, beta, base, total, lim, pt0,
+                                                      reinterpret_cast<T*>(Zc), RowLen<L>{}, L);
         } else {
             for (int base = 0; base < total; base += KU * blockDim.x)
-                first_stage0_chunk<T, D, L, KU, true>(a, op, tab, beta, base, total, lim, pt0,
-                                                      reinterpret_cast<T*>(Zc));
+                first_stage0_chunk<T, D, L, KU>(a, op, tab, beta, base, total, lim, pt0,
+                                                reinterpret_cast<T*>(Zc), RowLen<L>{}, L);
         }
     }
     lds_barrier();
@@ -1037,7 +1065,7 @@ __device__ __forceinline__ double last_epilogue_tile(const LastArgs<T>& a, const
     // the Chebyshev and Eyre-Milton epilogues hold three more vectors per point: smaller chunks
     constexpr int KU = (epi == EPI_CHEB || epi == EPI_EM) && ku_for(L) > KUH ? KUH : ku_for(L);
     for (int base = 0; base < total; base += KU * blockDim.x)
-        acc += last_epilogue_chunk<T, D, L, epi, KU>(a, tab, base, total, lim, pt0, Zr);
+        acc += last_epilogue_chunk<T, D, L, epi, KU>(a, tab, base, total, lim, pt0, Zr, RowLen<L>{}, L + 1);
     return acc;
 }
 
@@ -1124,9 +1152,9 @@ __global__ __launch_bounds__(kThreads) void k2_last_b(const LastArgs<T>* __restr
 // are then forward-transformed in place (row stride L + 1) and stored as the next body's first
 // spectrum.  This saves the next first pass's read of the iterate and one launch per body.
 // ------------------------------------------------------------------------------------------
-template <typename T, int D, int L, int epi, int KU>
+template <typename T, int D, int LT, int epi, int KU>
 __device__ __forceinline__ double lastfirst_chunk(const LastArgs<T>& a, const T* tab, const T* tabinv, int base,
-                                                  int total, int lim, long long pt0, T* Zr)
+                                                  int total, int lim, long long pt0, T* Zr, RowLen<LT> rl, int RS)
 {
     const unsigned npts = (unsigned)a.g.npts;  // 32-bit offsets: d |grid| < 2^31 here
     unsigned pt[KU];
@@ -1138,13 +1166,13 @@ __device__ __forceinline__ double lastfirst_chunk(const LastArgs<T>& a, const T*
         const int idx = base + u * (int)blockDim.x + (int)threadIdx.x;
         ok[u] = idx < lim;
         pt[u] = ok[u] ? (unsigned)(pt0 + idx) : 0u;
-        const int r = idx / L;
-        const int i = idx - r * L;
+        const int r = rl.row(idx);
+        const int i = idx - r * rl.len();
         at[u] = i;
 #pragma unroll
         for (int c = 0; c < D; c++) {
             const int q = r * D + c;
-            y[u][c] = ok[u] ? Zr[((q >> 1) * (L + 1) + i) * 2 + (q & 1)] : T(0);
+            y[u][c] = ok[u] ? Zr[((q >> 1) * RS + i) * 2 + (q & 1)] : T(0);
         }
     }
     T un[KU][D];
@@ -1239,11 +1267,11 @@ __device__ __forceinline__ double lastfirst_chunk(const LastArgs<T>& a, const T*
     for (int u = 0; u < KU; u++) {
         const int idx = base + u * (int)blockDim.x + (int)threadIdx.x;
         if (idx < total) {
-            const int r = idx / L;
+            const int r = rl.row(idx);
 #pragma unroll
             for (int c = 0; c < D; c++) {
                 const int q = r * D + c;
-                Zr[((q >> 1) * (L + 1) + at[u]) * 2 + (q & 1)] = ok[u] ? z[u][c] : T(0);
+                Zr[((q >> 1) * RS + at[u]) * 2 + (q & 1)] = ok[u] ? z[u][c] : T(0);
             }
         }
     }
@@ -1312,7 +1340,7 @@ __device__ __forceinline__ void lastfirst_body(const LastArgs<T>& a, int b, int 
         const int lim = left < total ? (int)left : total;
         constexpr int KU = epi == EPI_RICH ? (ku_for(L) > 3 ? 3 : ku_for(L)) : (ku_for(L) > 2 ? 2 : ku_for(L));
         for (int base = 0; base < total; base += KU * blockDim.x)
-            acc += lastfirst_chunk<T, D, L, epi, KU>(a, tab, tabinv, base, total, lim, pt0, Zr);
+            acc += lastfirst_chunk<T, D, L, epi, KU>(a, tab, tabinv, base, total, lim, pt0, Zr, RowLen<L>{}, L + 1);
         if ((a.rpb * D) & 1)  // the imaginary half of the last packed row is a zero row
             for (int i = threadIdx.x; i < L; i += blockDim.x) Sx[(npairs - 1) * (L + 1) + i].y = T(0);
     }
