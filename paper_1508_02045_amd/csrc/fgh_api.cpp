@@ -224,7 +224,7 @@ bool make_geo(int d, const int32_t* N, int rule, Geo* g)
 }
 
 struct Layout {
-    size_t tw64[3], tw32[3], SA, SB, vec64, vec32, partials, scalars, mask, coef64, coef32, sinc[3], twN[3], twM[3];
+    size_t tw64[3], tw32[3], SA, SB, vec64, vec32, partials, partials2, scalars, mask, coef64, coef32, sinc[3], twN[3], twM[3];
     size_t slab;  // argument tables of batched launches led by this plan
     size_t total;
     long long npart;
@@ -272,6 +272,7 @@ Layout make_layout(const Geo& g, const int32_t* N, int rule, int prec, int akind
     if (np < 512 * 18) np = 512 * 18;
     l.npart = np + 64;
     l.partials = take((size_t)l.npart * 8);
+    l.partials2 = take((size_t)std::max<long long>(g.rows, 1024) * 8);  // at most one per row, or the update's
     l.scalars = take(sizeof(Scalars));
     l.slab = take(kBatchSlabBytes);
     l.mask = take(16);
@@ -453,6 +454,7 @@ void fill_opplan_at(OpPlan* op, const Geo& g, bool f32, char* const tw[3], char*
     op->v2_mid = c.v2_mid;
     op->gen_row = op->gen_axis = op->gen_mid = false;
     op->partials = partials;
+    op->partials2 = nullptr;
     op->sc = sc;
     op->stream = stream;
 }
@@ -493,6 +495,7 @@ void fill_opplan(fgh_plan p, OpPlan* op, bool f32)
     fill_opplan_at(op, p->g, f32, tw, p->ws + p->lay.SA, p->ws + p->lay.SB,
                    reinterpret_cast<double*>(p->ws + p->lay.partials), reinterpret_cast<Scalars*>(p->ws + p->lay.scalars),
                    p->stream);
+    op->partials2 = reinterpret_cast<double*>(p->ws + p->lay.partials2);
 }
 
 // FGH_TUNE_LOG=1: the tuners print each candidate's time (three launches) to stderr.
@@ -674,8 +677,8 @@ fgh_status tune_first(fgh_plan p, OpPlan* op, bool f32, const void* x)
         std::lock_guard<std::mutex> lk(mu);
         auto it = cache.find(key);
         if (it != cache.end()) {
-            op->rpb_first = it->second;
-            op->lds_first_v2 = lds_of(it->second);
+            op->rpb_first = op->rpb_first_x = it->second;
+            op->lds_first_v2 = op->lds_first_x = lds_of(it->second);
             return FGH_OK;
         }
     }
@@ -721,8 +724,8 @@ fgh_status tune_first(fgh_plan p, OpPlan* op, bool f32, const void* x)
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (err != hipSuccess) return FGH_E_DEVICE;
-    op->rpb_first = best;
-    op->lds_first_v2 = lds_of(best);
+    op->rpb_first = op->rpb_first_x = best;
+    op->lds_first_v2 = op->lds_first_x = lds_of(best);
     std::lock_guard<std::mutex> lk(mu);
     cache[key] = best;
     return FGH_OK;
@@ -1039,36 +1042,99 @@ fgh_status run_loop(fgh_plan p, const OpPlan& op, Body body, uint64_t key, bool 
     return FGH_OK;
 }
 
-// One body of Algorithm 2: p <- r + beta p (beta = 0 before the first body, p = r), q = C p,
-// alpha = (r, r) / (q, p), x += alpha p, r -= alpha q, beta = (r_new, r_new) / (r, r).  The
-// coefficients are left in the loop's scalar block.  With defer_x the body's x += alpha p is left
-// to the next body's first pass, which reads p there anyway before replacing it (one vector
-// stream less per body; the same operation on the same values), and the loop's last update to
-// run_cg_x after the loop.
+// Whether a loop's reductions are left to the kernels that need them (see ApplyArgs::defer_redop,
+// ApplyArgs::cg_pq and UpdateArgs::qp).  The host then sees a body's stopping test one body later, so a
+// loop may launch one more chunk of bodies that return at once.  Not while a history recorder
+// reads the body count between bodies.  FGH_DEFER=0 turns this off.
+bool defer_reduction(fgh_plan p)
+{
+    const char* v = std::getenv("FGH_DEFER");
+    return !p->hist_fn && !(v && v[0] == '0');
+}
+
+// Whether every one of `blocks` workgroups may add up n partial sums for itself instead of a reduction
+// launch (about 4 us and a gap): the sums come from the L2, so their volume is bounded (32 MB, a few
+// us over the whole launch) and so is the latency each workgroup pays (8 loads per thread).
+bool sum_in_kernel(long long n, long long blocks) { return n <= 2048 && n * blocks <= (4LL << 20); }
+
+// How a CG body's scalars are completed.
+struct CgPlan {
+    bool defer_x;    // x += alpha p by the next body's first pass (the loop's last one by run_cg_x)
+    bool defer_end;  // beta, and the body's end, by the next body's first two passes
+    bool pq_next;    // FP64: alpha by the pass after the first one
+    bool qp_update;  // FP32: alpha by the update kernel
+};
+
+CgPlan cg_plan(const OpPlan& op, long long n, bool fp64, bool defer_x, bool defer)
+{
+    const long long r1 = defer_x ? op.rpb_first_x : op.rpb_first;
+    const long long first = (op.g.rows + r1 - 1) / r1, last = (op.g.rows + op.rpb - 1) / op.rpb;
+    const long long upd = cg_update_blocks(n);
+    CgPlan c{defer_x, false, false, false};
+    if (defer) {
+        c.defer_end = sum_in_kernel(fp64 ? last : upd, first);
+        c.pq_next = fp64;
+        c.qp_update = !fp64 && sum_in_kernel(last, upd);
+    }
+    return c;
+}
+
+// The application of a CG body: p <- r + beta p (beta = 0 before the first body, p = r), A p, and
+//   FP64: alpha = (r, r) / (A p, p) from the first pass -- p is in the range of the projection G, so
+//     (G A p, p) = (A p, p) -- so that the last pass updates r itself: q = G A p is neither written
+//     nor read again, and the body has no update kernel (243^3: 1033 of 6200 MB per body);
+//   FP32: q = G A p and (q, p) from the last pass; the update kernel follows.
 template <typename T>
-hipError_t cg_body(const OpPlan& op, long long n, T* x, T* r, T* pv, T* q, bool defer_x)
+ApplyArgs cg_apply_args(const OpPlan& op, const CgPlan& c, T* x, T* r, T* pv, T* q)
 {
     ApplyArgs a;
     a.op = OP_AP_CG;
     a.p_cg = pv;
     a.r_cg = r;
-    a.x_cg = defer_x ? x : nullptr;
-    a.epi = EPI_CG;
-    a.eq = q;
+    a.x_cg = c.defer_x ? x : nullptr;
     a.ep = pv;
     a.loop = true;
+    if (sizeof(T) == 8) {
+        a.epi = c.defer_x ? EPI_CGR : EPI_CGRX;
+        a.er = r;
+        a.ex = x;
+        a.cg_pq = c.pq_next ? 2 : 1;
+        a.end_part = op.partials;
+    } else {
+        a.epi = EPI_CG;
+        a.eq = q;
+        a.end_part = op.partials2;
+        a.nend = cg_update_blocks((long long)op.g.d * op.g.npts);
+    }
+    a.defer_redop = c.defer_end ? RED_CG_END : -1;
+    return a;
+}
+
+UpdateArgs<float> cg_update_args(const OpPlan& op, const CgPlan& c, long long n, float* x, float* r, const float* pv,
+                                 const float* q, int nb_last)
+{
+    return UpdateArgs<float>{n, c.defer_x ? nullptr : x, r, pv, q, op.sc, op.partials2, op.partials,
+                             c.qp_update ? nb_last : 0, c.defer_end ? 1 : 0};
+}
+
+// One body of Algorithm 2; the coefficients are left in the loop's scalar block.
+template <typename T>
+hipError_t cg_body(const OpPlan& op, const CgPlan& c, long long n, T* x, T* r, T* pv, T* q)
+{
     int nb = 0;
-    hipError_t e = run_apply<T>(op, a, &nb);
+    hipError_t e = run_apply<T>(op, cg_apply_args<T>(op, c, x, r, pv, q), &nb);
     if (e != hipSuccess) return e;
-    if ((e = run_reduce_async(op, nb, RED_CG_ALPHA)) != hipSuccess) return e;
-    if ((e = run_cg_update<T>(op, n, defer_x ? nullptr : x, r, pv, q)) != hipSuccess) return e;
-    return run_reduce_async(op, vec_blocks(), RED_CG_END);
+    if constexpr (sizeof(T) == 8) {
+        return c.defer_end ? hipSuccess : run_reduce_async(op, nb, RED_CG_END);
+    } else {
+        if (!c.qp_update && (e = run_reduce_async(op, nb, RED_CG_ALPHA)) != hipSuccess) return e;
+        if ((e = run_cg_update<T>(op, cg_update_args(op, c, n, x, r, pv, q, nb))) != hipSuccess) return e;
+        return c.defer_end ? hipSuccess : run_reduce_async(op, cg_update_blocks(n), RED_CG_END, op.partials2);
+    }
 }
 
 // Conjugate gradients (Algorithm 2) for C x = b with b already in r, x = 0 on entry.  Stops when
-// ||r_m|| <= tol_rel ||b|| (recursive residual) or after `fixed` bodies.  The iterate update is
-// deferred to the next body (cg_body) on large grids unless a history recorder reads x between
-// bodies.
+// ||r_m|| <= tol_rel ||b|| (recursive residual) or after `fixed` bodies.
 template <typename T>
 fgh_status cg_core(fgh_plan p, T* x, T* r, T* pv, T* q, double tol_rel, int max_iter, int fixed, SolveOut* out)
 {
@@ -1087,12 +1153,16 @@ fgh_status cg_core(fgh_plan p, T* x, T* r, T* pv, T* q, double tol_rel, int max_
     const int limit = fixed > 0 ? fixed : max_iter;
     // alpha = 0 before the first body: its deferred update leaves x as it is
     HIPOK(run_init_loop(op, bb, 0.0, 0.0, fixed > 0 ? -1.0 : tol_rel * normb, S, 0.0, 0.0, 0.0, limit));
-    // deferral saves the update's x stream from HBM, on grids where it reaches HBM (cg_defers;
-    // FGH_CG_DEFER=1 or 0 forces it on or off)
+    // x += alpha p is left to the next body's first pass, which reads p there anyway before replacing
+    // it (the same operation on the same values), unless a history recorder reads x between bodies;
+    // in FP32 only on grids where the update kernel's x stream reaches HBM (cg_defers).
+    // FGH_CG_DEFER=1 or 0 forces it on or off.
     const int force = env_int_any("FGH_CG_DEFER", -1);
-    const bool defer_x = !p->hist_fn && (force >= 0 ? force == 1 : cg_defers(n, sizeof(T)));
-    auto body = [&]() { return cg_body<T>(op, n, x, r, pv, q, defer_x); };
-    const uint64_t key = key_of({defer_x ? 2u : 1u, sizeof(T), bits(x), bits(r), bits(pv), bits(q)});
+    const bool defer_x = !p->hist_fn && (force >= 0 ? force == 1 : sizeof(T) == 8 || cg_defers(n, sizeof(T)));
+    const CgPlan c = cg_plan(op, n, sizeof(T) == 8, defer_x, defer_reduction(p));
+    auto body = [&]() { return cg_body<T>(op, c, n, x, r, pv, q); };
+    const uint64_t key = key_of({defer_x ? 2u : 1u, sizeof(T), bits(x), bits(r), bits(pv), bits(q),
+                                 (uint64_t)c.defer_end, (uint64_t)(c.pq_next || c.qp_update)});
     const fgh_status s = run_loop(p, op, body, key, fixed > 0, normb, out);
     // the last body's x += alpha p (bodies after the stop return at once and leave alpha and p)
     if (s == FGH_OK && defer_x) HIPOK(run_cg_x<T>(op, n, x, pv));
@@ -1107,15 +1177,6 @@ bool fuse_loop(fgh_plan p, const OpPlan& op)
 {
     const char* v = std::getenv("FGH_FUSE");
     return fusable(op) && !p->hist_fn && !(v && v[0] == '0');
-}
-
-// Deferred loop reductions (see ApplyArgs::defer_redop): with fused bodies in 3D with the
-// specialised axis kernels.  The host then sees a body's stopping test one body later, so a loop
-// may launch one more chunk of bodies that return at once.  FGH_DEFER=0 turns this off.
-bool defer_reduction(const OpPlan& op, bool fuse)
-{
-    const char* v = std::getenv("FGH_DEFER");
-    return fuse && op.g.d == 3 && op.v2_axis && op.v2_row && !(v && v[0] == '0');
 }
 
 // The loop's prologue of a fused loop: the first body's first pass alone.
@@ -1167,8 +1228,9 @@ fgh_status cheb_core(fgh_plan p, T* x, T* r, T* pv, double tol_rel, int max_iter
         a.skip_first = true;
         a.next_op = OP_AX;
     }
-    const bool defer = defer_reduction(op, fuse);
+    const bool defer = defer_reduction(p);
     a.defer_redop = defer ? RED_CHEB_END : -1;
+    a.end_part = op.partials;
     auto body = [&]() -> hipError_t {
         int nb = 0;
         hipError_t e = run_apply<T>(op, a, &nb);
@@ -1204,8 +1266,9 @@ fgh_status rich_core(fgh_plan p, T* x, const double* E0, double thr, int max_ite
         a.skip_first = true;
         a.next_op = OP_AX;
     }
-    const bool defer = defer_reduction(op, fuse);
+    const bool defer = defer_reduction(p);
     a.defer_redop = defer ? RED_STEP_END : -1;
+    a.end_part = op.partials;
     auto body = [&]() -> hipError_t {
         int nb = 0;
         hipError_t e = run_apply<T>(op, a, &nb);
@@ -1245,8 +1308,9 @@ fgh_status em_core(fgh_plan p, T* x, const double* E, const T* src, double thr, 
         a.skip_first = true;
         a.next_op = OP_EM;
     }
-    const bool defer = defer_reduction(op, fuse);
+    const bool defer = defer_reduction(p);
     a.defer_redop = defer ? RED_STEP_END : -1;
+    a.end_part = op.partials;
     auto body = [&]() -> hipError_t {
         int nb = 0;
         hipError_t e = run_apply<T>(op, a, &nb);
@@ -1793,6 +1857,7 @@ fgh_status cg_inner_batch(const std::vector<BatchMember*>& A, int max_iter, hipS
     std::vector<ReduceArgs> r1(nb), r2(nb);
     std::vector<UpdateArgs<float>> up(nb);
     std::vector<double> scale(nb);
+    CgPlan c{};  // the same for every member: they share their launch shape
     for (int k = 0; k < nb; k++) {
         fgh_plan p = A[k]->p;
         const OpPlan& op = p->op32;
@@ -1806,18 +1871,11 @@ fgh_status cg_inner_batch(const std::vector<BatchMember*>& A, int max_iter, hipS
         if (st) return st;
         scale[k] = std::sqrt(bb / S);
         HIPOK(run_init_loop(op, bb, 0.0, 0.0, A[k]->eta * scale[k], S, 0.0, 0.0, 0.0, max_iter));
-        ApplyArgs a;
-        a.op = OP_AP_CG;
-        a.p_cg = p->p32;
-        a.r_cg = p->r32;
-        a.epi = EPI_CG;
-        a.eq = p->q32;
-        a.ep = p->p32;
-        a.loop = true;
-        HIPOK(build_bundle<float>(op, a, &bu[k]));
+        c = cg_plan(op, n, false, false, defer_reduction(p));
+        HIPOK(build_bundle<float>(op, cg_apply_args<float>(op, c, p->x32, p->r32, p->p32, p->q32), &bu[k]));
         r1[k] = ReduceArgs{op.partials, (int)bu[k].nblk_last, op.sc};
-        r2[k] = ReduceArgs{op.partials, vec_blocks(), op.sc};
-        up[k] = UpdateArgs<float>{n, p->x32, p->r32, p->p32, p->q32, op.sc, op.partials};
+        r2[k] = ReduceArgs{op.partials2, cg_update_blocks(n), op.sc};
+        up[k] = cg_update_args(op, c, n, p->x32, p->r32, p->p32, p->q32, (int)bu[k].nblk_last);
     }
     BatchTables<float> t;
     fgh_plan lead = A[0]->p;
@@ -1827,11 +1885,11 @@ fgh_status cg_inner_batch(const std::vector<BatchMember*>& A, int max_iter, hipS
     auto body = [&]() -> hipError_t {
         hipError_t e = run_apply_batch<float>(op0, bu[0], t, nb);
         if (e != hipSuccess) return e;
-        if ((e = run_reduce_batch(s, t.red, nb, RED_CG_ALPHA)) != hipSuccess) return e;
-        if ((e = run_cg_update_batch<float>(s, t.upd, nb)) != hipSuccess) return e;
-        return run_reduce_batch(s, t.red2, nb, RED_CG_END);
+        if (!c.qp_update && (e = run_reduce_batch(s, t.red, nb, RED_CG_ALPHA)) != hipSuccess) return e;
+        if ((e = run_cg_update_batch<float>(s, t.upd, up[0].n, nb)) != hipSuccess) return e;
+        return c.defer_end ? hipSuccess : run_reduce_batch(s, t.red2, nb, RED_CG_END);
     };
-    return run_loop_batch(lead, A, s, body, batch_key(21, A), scale, outs);
+    return run_loop_batch(lead, A, s, body, batch_key(21 + 16 * c.qp_update + 32 * c.defer_end, A), scale, outs);
 }
 
 // The inner FP32 Eyre-Milton correction solves of the active members (em_core's correction
@@ -1868,8 +1926,9 @@ fgh_status em_inner_batch(const std::vector<BatchMember*>& A, int max_iter, hipS
         HIPOK(build_bundle<float>(op, ap, &pro[k]));
         a.skip_first = true;
         a.next_op = OP_EM;
-        defer = defer_reduction(op, true);
+        defer = defer_reduction(p);
         a.defer_redop = defer ? RED_STEP_END : -1;
+        a.end_part = op.partials;
         HIPOK(build_bundle<float>(op, a, &bu[k]));
         bu[k].fa = pro[k].fa;  // the body skips its first pass: the table slot holds the prologue's
         r1[k] = ReduceArgs{op.partials, (int)bu[k].nblk_last, op.sc};
@@ -2800,9 +2859,11 @@ fgh_status fgh_estimate_bounds(fgh_plan p, const double* E, int iters, double* e
     HIPOK(run_copy<double>(p->stream, n, p->p64, p->r64));
     HIPOK(run_init_loop(op, bb, 0.0, 0.0, -1.0, S, 0.0, 0.0, 0.0, iters));
     const Scalars* h = reinterpret_cast<const Scalars*>(p->host_buf);
+    CgPlan c = cg_plan(op, n, true, false, true);
+    c.defer_end = false;  // alpha and beta are read after every body
     std::vector<double> al, be;
     for (int k = 0; k < iters; k++) {
-        HIPOK(cg_body<double>(op, n, e, p->r64, p->p64, p->q64, false));
+        HIPOK(cg_body<double>(op, c, n, e, p->r64, p->p64, p->q64));
         HIPOK(hipMemcpyAsync(p->host_buf, op.sc, sizeof(Scalars), hipMemcpyDeviceToHost, op.stream));
         HIPOK(hipStreamSynchronize(op.stream));
         if (!(h->alpha > 0.0) || !std::isfinite(h->alpha)) {

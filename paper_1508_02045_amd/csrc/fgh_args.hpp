@@ -79,9 +79,26 @@ __device__ __forceinline__ void sym_shift_solve(const T* a, T w, const T* rhs, T
     }
 }
 
+// Loop reductions left to the pass that follows a first pass (the strided pass in 3D, the middle pass
+// in 2D): the previous body's end from nend partial sums (while Scalars::pend is set), then CG's
+// alpha from npq partial sums of (A p, p).  A workgroup of its own does it, dispatched first, so
+// that its chain of latencies runs beside the tiles.  sc = nullptr: nothing is left.
+struct Pending {
+    Scalars* sc;
+    const double* end;
+    const double* pq;
+    int nend, npq;
+    // workgroups before those of the tiles: one per XCD, so that a tile's XCD stays that of its rank
+    static constexpr int kBlocks = 8;
+    __host__ __device__ int blocks() const { return sc ? kBlocks : 0; }
+};
+
 template <typename T>
 struct FirstArgs {
     const int* done;  // the loop's stop flag (nullptr: always run)
+    // OP_AP_CG: the nend partial sums of the previous body's (r, r), read while its end is pending
+    // (Scalars::pend; nullptr: beta is in the scalar block)
+    const double* end_part;
     Geo g;
     Axis ax;
     int rpb, npen;
@@ -92,6 +109,8 @@ struct FirstArgs {
     // p on entry, before p is replaced (nullptr: x is updated elsewhere)
     T* xd;
     const Scalars* sc;
+    int nend;
+    double* pq_part;  // OP_AP_CG: the partial sums of (A p, p), one per workgroup (nullptr: not wanted)
     double E[3];
     double omega;
     CoefArgs A;
@@ -102,6 +121,7 @@ struct FirstArgs {
 template <typename T>
 struct AxisArgs {
     const int* done;  // the loop's stop flag (nullptr: always run)
+    Pending pend;     // loop reductions left to this pass
     Axis ax;
     int nin, nout;          // stored counts along the axis
     int bin, bout;          // 1: stored index is a band index (frequency signed(s, n)), 0: position
@@ -110,13 +130,13 @@ struct AxisArgs {
     const cpx<T>* in;
     cpx<T>* out;
     const cpx<T>* twg;
-    Scalars* red_sc;          // non-null: workgroup 0 completes a deferred loop reduction first
-    const double* partials;
+    int outer, comps;         // the launch: ntiles x outer x comps workgroups, after pend's
 };
 
 template <typename T>
 struct MidArgs {
     const int* done;  // the loop's stop flag (nullptr: always run)
+    Pending pend;     // 2D: loop reductions left to this pass (its workgroups precede the ntiles of the pass)
     Axis ax;
     int B0, cols, Hb, B1, P, ntiles;
     int ys;        // specialised kernel: LDS stride of a column (complex elements, >= L)
@@ -129,7 +149,7 @@ struct MidArgs {
 template <typename T>
 struct LastArgs {
     const int* done;  // the loop's stop flag (nullptr: always run)
-    const Scalars* sc;  // Chebyshev alpha, beta (device) when non-null
+    const Scalars* sc;  // the loop scalars: CG alpha; Chebyshev alpha, beta when non-null
     Geo g;
     Axis ax;
     int rpb, npen;

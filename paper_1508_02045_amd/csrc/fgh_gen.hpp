@@ -321,32 +321,38 @@ __device__ __forceinline__ void load_half_spectra(const Geo& g, int L, const cpx
 template <typename T, int D, int NI>
 __global__ __launch_bounds__(kGenMaxThreads) void kg_first(FirstArgs<T> a, int op)
 {
-    if (a.done && *a.done) return;
+    __shared__ double red[2 * kGenMaxThreads / 64];
+    T beta = T(0);
+    if (!a.end_part && a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, npen = a.npen;
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* Z = tw + L;
     T* tab = reinterpret_cast<T*>(Z + npen * L);
+    const long long row0 = xcd_tile(blockIdx.x, gridDim.x) * a.rpb;
+    const int nrows = (int)(a.g.rows - row0 < a.rpb ? a.g.rows - row0 : a.rpb);
     for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
     if (a.A.kind == AK_PHASE)
         for (int m = threadIdx.x; m < kMaxPhases * 6; m += blockDim.x) tab[m] = T(a.A.tab[m / 6][m % 6]);
     if ((a.rpb * D) & 1)  // the imaginary half of the last packed row is a zero row
         for (int i = threadIdx.x; i < L; i += blockDim.x) Z[(npen - 1) * L + i].y = T(0);
+    if (op == OP_AP_CG && !first_beta(a, red, &beta)) return;
     lds_barrier();
-    const long long row0 = xcd_tile(blockIdx.x, gridDim.x) * a.rpb;
-    const int nrows = (int)(a.g.rows - row0 < a.rpb ? a.g.rows - row0 : a.rpb);
-    const T beta = (op == OP_AP_CG) ? T(a.sc->beta) : T(0);
+    double acc = 0.0;
     const int total = a.rpb * L, lim = nrows * L;
     const RowLen<0> rl{L, 1.0f / (float)L};
     constexpr int KU = 3;
+    T* Zr = reinterpret_cast<T*>(Z);
     if (op == OP_AP_CG && a.xd) {
         for (int base = 0; base < total; base += KU * blockDim.x)
-            first_stage0_chunk<T, D, 0, KU, true>(a, op, tab, beta, base, total, lim, row0 * L,
-                                                  reinterpret_cast<T*>(Z), rl, L);
+            first_stage0_chunk<T, D, 0, KU, true>(a, op, tab, beta, base, total, lim, row0 * L, Zr, rl, L, acc);
     } else {
         for (int base = 0; base < total; base += KU * blockDim.x)
-            first_stage0_chunk<T, D, 0, KU>(a, op, tab, beta, base, total, lim, row0 * L, reinterpret_cast<T*>(Z), rl,
-                                            L);
+            first_stage0_chunk<T, D, 0, KU>(a, op, tab, beta, base, total, lim, row0 * L, Zr, rl, L, acc);
+    }
+    if (sizeof(T) == 8 && a.pq_part) {
+        const double tot = block_sum(acc, red);
+        if (threadIdx.x == 0) a.pq_part[blockIdx.x] = tot;
     }
     lds_barrier();
     row_transform<T, false, NI>(Z, a.ax, npen, tw);
@@ -372,13 +378,19 @@ __global__ __launch_bounds__(kGenMaxThreads) void kg_last(LastArgs<T> a)
     lds_barrier();
     row_transform<T, true, NI>(Z, a.ax, npen, tw);
     const RowLen<0> rl{L, 1.0f / (float)L};
-    constexpr int KU = (epi == EPI_CHEB || epi == EPI_EM) ? 2 : 3;
+    constexpr int KU = (epi == EPI_CHEB || epi == EPI_EM || epi == EPI_CGRX) ? 2 : 3;
     double acc = 0.0;
     for (int base = 0; base < a.rpb * L; base += KU * blockDim.x)
-        acc += last_epilogue_chunk<T, D, 0, epi, KU>(a, tab, base, a.rpb * L, nrows * L, row0 * L,
-                                                     reinterpret_cast<const T*>(Z), rl, L);
+        acc = last_epilogue_chunk<T, D, 0, epi, KU>(a, tab, base, a.rpb * L, nrows * L, row0 * L,
+                                                    reinterpret_cast<const T*>(Z), rl, L, acc);
     const double tot = block_sum(acc, red);
-    if (threadIdx.x == 0) a.partials[blockIdx.x] = tot;
+    if (threadIdx.x == 0) {
+        a.partials[blockIdx.x] = tot;
+        if (a.defer_sc && blockIdx.x == 0) {
+            a.defer_sc->pend = 1;
+            a.defer_sc->pend_op = a.redop;
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -437,18 +449,15 @@ __device__ __forceinline__ void axis_b_reg(const AxisArgs<T>& a, cpx<T>* out, in
 template <typename T, bool INV, int NI>
 __global__ __launch_bounds__(kGenMaxThreads) void kg_axis(AxisArgs<T> a, int B)
 {
-    if (a.red_sc && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
-        __shared__ double red[kGenMaxThreads / 64];
-        finish_deferred(a.red_sc, a.partials, red);
-    }
+    int b = blockIdx.x;
+    if (a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, P = a.P, q = a.ax.q, p = a.ax.p;
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* X = tw + L;
-    const int gx = gridDim.x, gy = gridDim.y;
-    const long long lin = xcd_tile(blockIdx.x + (long long)gx * (blockIdx.y + (long long)gy * blockIdx.z),
-                                   (long long)gx * gy * gridDim.z);
+    const int gx = a.ntiles, gy = a.outer;
+    const long long lin = xcd_tile(b, (long long)gx * gy * a.comps);
     const int tile = (int)(lin % gx);
     const int o = (int)((lin / gx) % gy);
     const int c = (int)(lin / ((long long)gx * gy));
@@ -618,12 +627,14 @@ __device__ __forceinline__ void mid_b_split(const MidArgs<T>& a, int j0, float i
 template <typename T, int D, int MULT, int NI>
 __global__ __launch_bounds__(kGenMaxThreads) void kg_middle(MidArgs<T> a)
 {
+    int b = blockIdx.x;
+    if (D == 2 && a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, P = a.P, q = a.ax.q, p = a.ax.p, NS = 2 * P;
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* X = tw + L;
-    const int j0 = (int)xcd_tile(blockIdx.x, gridDim.x) * P;
+    const int j0 = (int)xcd_tile(b, a.ntiles) * P;
     for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
     const float iP = 1.0f / (float)P;
     const int tot = L * P;

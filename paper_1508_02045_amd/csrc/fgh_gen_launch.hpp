@@ -46,23 +46,27 @@ static hipError_t gen_last_epi(const OpPlan& op, const LastArgs<T>& la, unsigned
 #undef C
 }
 
+// Single precision has these passes for fgh_apply_f32 alone (plain epilogue, G^ multiplier).
 template <typename T>
 hipError_t gen_last(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned nblk)
 {
-    switch (epi) {
-        case EPI_STORE: return gen_last_epi<T, EPI_STORE>(op, la, nblk);
-        case EPI_RICH: return gen_last_epi<T, EPI_RICH>(op, la, nblk);
-        case EPI_CG: return gen_last_epi<T, EPI_CG>(op, la, nblk);
-        case EPI_CHEB: return gen_last_epi<T, EPI_CHEB>(op, la, nblk);
-        case EPI_EM: return gen_last_epi<T, EPI_EM>(op, la, nblk);
+    if (epi == EPI_STORE) return gen_last_epi<T, EPI_STORE>(op, la, nblk);
+    if constexpr (sizeof(T) == 8) {
+        switch (epi) {
+            case EPI_RICH: return gen_last_epi<T, EPI_RICH>(op, la, nblk);
+            case EPI_CGR: return gen_last_epi<T, EPI_CGR>(op, la, nblk);
+            case EPI_CGRX: return gen_last_epi<T, EPI_CGRX>(op, la, nblk);
+            case EPI_CHEB: return gen_last_epi<T, EPI_CHEB>(op, la, nblk);
+            case EPI_EM: return gen_last_epi<T, EPI_EM>(op, la, nblk);
+        }
     }
     return hipErrorInvalidValue;
 }
 
 template <typename T, int NI>
-static hipError_t gen_axis_ni(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer, int B)
+static hipError_t gen_axis_ni(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int B)
 {
-    const dim3 grid(xa.ntiles, outer, op.g.d);
+    const dim3 grid(axis_blocks(xa));
     if (inv)
         LAUNCH_LDS_T((kg_axis<T, true, NI>), grid, op.th_axis, op.lds_axis, op.stream, xa, B);
     else
@@ -71,9 +75,9 @@ static hipError_t gen_axis_ni(const OpPlan& op, const AxisArgs<T>& xa, bool inv,
 }
 
 template <typename T>
-hipError_t gen_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer, int B)
+hipError_t gen_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int B)
 {
-#define C(N) gen_axis_ni<T, N>(op, xa, inv, outer, B)
+#define C(N) gen_axis_ni<T, N>(op, xa, inv, B)
     FGH_GEN_NI(op.ni_axis, C);
 #undef C
 }
@@ -81,11 +85,15 @@ hipError_t gen_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer
 template <typename T, int D, int NI>
 static hipError_t gen_middle_ni(const OpPlan& op, const MidArgs<T>& ma, int mult)
 {
-    if (mult == MULT_G)
-        LAUNCH_LDS_T((kg_middle<T, D, MULT_G, NI>), dim3(ma.ntiles), op.th_mid, op.lds_mid, op.stream, ma);
-    else
-        LAUNCH_LDS_T((kg_middle<T, D, MULT_EM, NI>), dim3(ma.ntiles), op.th_mid, op.lds_mid, op.stream, ma);
-    return hipGetLastError();
+    if (mult == MULT_G) {
+        LAUNCH_LDS_T((kg_middle<T, D, MULT_G, NI>), dim3(ma.ntiles + ma.pend.blocks()), op.th_mid, op.lds_mid, op.stream, ma);
+        return hipGetLastError();
+    }
+    if constexpr (sizeof(T) == 8) {
+        LAUNCH_LDS_T((kg_middle<T, D, MULT_EM, NI>), dim3(ma.ntiles + ma.pend.blocks()), op.th_mid, op.lds_mid, op.stream, ma);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -99,7 +107,7 @@ hipError_t gen_middle(const OpPlan& op, const MidArgs<T>& ma, int mult)
 #define FGH_GEN_INSTANTIATE(T)                                                             \
     template hipError_t gen_first<T>(const OpPlan&, const FirstArgs<T>&, int, unsigned);   \
     template hipError_t gen_last<T>(const OpPlan&, const LastArgs<T>&, int, unsigned);     \
-    template hipError_t gen_axis<T>(const OpPlan&, const AxisArgs<T>&, bool, int, int);    \
+    template hipError_t gen_axis<T>(const OpPlan&, const AxisArgs<T>&, bool, int);         \
     template hipError_t gen_middle<T>(const OpPlan&, const MidArgs<T>&, int);
 
 }  // namespace fgh

@@ -66,7 +66,9 @@ enum Epi : int {
     EPI_RICH = 1,   // step = -w (G A (E + x)); x += step; acc += step.step
     EPI_CG = 2,     // q = G A p; acc += q.p
     EPI_CHEB = 3,   // r -= alpha q; x += alpha p; p = r - beta p; acc += r.r
-    EPI_EM = 4      // x_new = (A + wI)^{-1} (y + 2 w E); acc += |x_new - x|^2; x = x_new
+    EPI_EM = 4,     // x_new = (A + wI)^{-1} (y + 2 w E); acc += |x_new - x|^2; x = x_new
+    EPI_CGR = 5,    // r -= alpha (G A p); acc += r.r
+    EPI_CGRX = 6    // the same and x += alpha p
 };
 
 // Device-resident solver state.  The loop kernels of an iteration return at once when done != 0,
@@ -87,7 +89,7 @@ struct Scalars {
     int done;           // 0 running, 1 stopping test met, 2 iteration cap, 3 diverged
     int m;              // loop bodies executed
     int limit;          // cap on m
-    int pend_n;         // partial sums of a loop reduction deferred to the next body (0: none)
+    int pend;           // 1: the loop reduction that ends the last body is left to the next one
     int pend_op;        //   and its RedOp
     double aux[40];     // [0, 16): loads for fgh_effective; [16, 40): multi-value reductions
 };

@@ -21,7 +21,10 @@ namespace fgh {
 template <typename T, int D, int AK, int OP>
 __global__ __launch_bounds__(kThreads) void k_first(FirstArgs<T> a)
 {
-    if (a.done && *a.done) return;
+    __shared__ double red[2 * kThreads / 64];
+    T beta = T(0);
+    if (!a.end_part && a.done && *a.done) return;
+    if (OP == OP_AP_CG && !first_beta(a, red, &beta)) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L;
     const int npen = a.npen;
@@ -37,7 +40,7 @@ __global__ __launch_bounds__(kThreads) void k_first(FirstArgs<T> a)
     if ((a.rpb * D) & 1)
         for (int i = threadIdx.x; i < L; i += blockDim.x) b0[(npen - 1) * L + i].y = T(0);
     __syncthreads();
-    const T beta = (OP == OP_AP_CG) ? T(a.sc->beta) : T(0);
+    double acc = 0.0;
     for (int idx = threadIdx.x; idx < a.rpb * L; idx += blockDim.x) {
         const int r = idx / L;
         const int i = idx - r * L;
@@ -72,6 +75,10 @@ __global__ __launch_bounds__(kThreads) void k_first(FirstArgs<T> a)
 #pragma unroll
                     for (int c = 0; c < D; c++) z[c] -= T(a.omega) * u[c];
                 }
+                if (sizeof(T) == 8 && OP == OP_AP_CG) {
+#pragma unroll
+                    for (int c = 0; c < D; c++) acc += double(z[c]) * double(u[c]);
+                }
             }
         } else {
 #pragma unroll
@@ -85,6 +92,10 @@ __global__ __launch_bounds__(kThreads) void k_first(FirstArgs<T> a)
             else
                 b0[(pp >> 1) * L + i].x = z[c];
         }
+    }
+    if (sizeof(T) == 8 && a.pq_part) {
+        const double tot = block_sum(acc, red);
+        if (threadIdx.x == 0) a.pq_part[blockIdx.x] = tot;
     }
     __syncthreads();
     cpx<T>* res = fft_lds<T, false>(b0, b1, a.ax, npen, tw);
@@ -117,6 +128,8 @@ __global__ __launch_bounds__(kThreads) void k_first(FirstArgs<T> a)
 template <typename T, bool INV>
 __global__ __launch_bounds__(kThreads) void k_axis(AxisArgs<T> a)
 {
+    int b = blockIdx.x;
+    if (a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L;
@@ -124,7 +137,8 @@ __global__ __launch_bounds__(kThreads) void k_axis(AxisArgs<T> a)
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* b0 = tw + L;
     cpx<T>* b1 = b0 + P * L;
-    const int tile = blockIdx.x, o = blockIdx.y, c = blockIdx.z;
+    const int tile = b % a.ntiles, oc = b / a.ntiles;
+    const int o = oc % a.outer, c = oc / a.outer;
     for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
     if (a.nin < L)
         for (int m = threadIdx.x; m < P * L; m += blockDim.x) b0[m] = {T(0), T(0)};
@@ -162,6 +176,9 @@ __global__ __launch_bounds__(kThreads) void k_axis(AxisArgs<T> a)
 template <typename T, int D, int MULT>
 __global__ __launch_bounds__(kThreads) void k_middle(MidArgs<T> a)
 {
+    int tile = blockIdx.x;
+    if (D == 2 && a.pend.sc && (tile -= Pending::kBlocks) < 0)
+        return finish_pending(a.pend, tile + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L;
@@ -169,7 +186,6 @@ __global__ __launch_bounds__(kThreads) void k_middle(MidArgs<T> a)
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* reg = tw + L;
     const int PL = P * L;
-    const int tile = blockIdx.x;
     for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
     for (int idx = threadIdx.x; idx < D * PL; idx += blockDim.x) {
         const int c = idx / PL;
@@ -349,6 +365,16 @@ __global__ __launch_bounds__(kThreads) void k_last(LastArgs<T> a)
                 a.q[c * npts + pt] = y[c];
                 acc += double(y[c]) * double(a.p[c * npts + pt]);
             }
+        } else if (EPI == EPI_CGR || EPI == EPI_CGRX) {
+            const T al = T(a.sc->alpha);
+#pragma unroll
+            for (int c = 0; c < D; c++) {
+                const long long o = c * npts + pt;
+                if (EPI == EPI_CGRX) a.x[o] = fma(al, a.p[o], a.x[o]);
+                const T rv = a.r[o] - al * y[c];
+                a.r[o] = rv;
+                acc += double(rv) * double(rv);
+            }
         } else if (EPI == EPI_CHEB) {
             const T al = T(a.sc ? a.sc->alpha : a.alpha), be = T(a.sc ? a.sc->beta : a.beta);
 #pragma unroll
@@ -396,7 +422,13 @@ __global__ __launch_bounds__(kThreads) void k_last(LastArgs<T> a)
         }
     }
     const double tot = block_sum(acc, red);
-    if (threadIdx.x == 0) a.partials[blockIdx.x] = tot;
+    if (threadIdx.x == 0) {
+        a.partials[blockIdx.x] = tot;
+        if (a.defer_sc && blockIdx.x == 0) {
+            a.defer_sc->pend = 1;
+            a.defer_sc->pend_op = a.redop;
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -404,10 +436,10 @@ __global__ __launch_bounds__(kThreads) void k_last(LastArgs<T> a)
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ void reduce_body(const double* __restrict__ partials, int n, Scalars* s, int op)
 {
-    __shared__ double red[kThreads / 64];
+    __shared__ double red[2 * kThreads / 64];
     const bool in_loop = op == RED_CG_ALPHA || op == RED_CG_END || op == RED_STEP_END || op == RED_CHEB_END;
     if (in_loop && s->done) return;
-    const double tot = block_sum(sum_partials(partials, n), red);
+    const double tot = sum_partials(partials, n, red);
     if (threadIdx.x == 0) apply_redop(s, op, tot);
 }
 
@@ -439,7 +471,7 @@ __global__ void k_init_loop(Scalars* s, double rr, double alpha, double beta, do
     s->m = 0;
     s->limit = limit;
     s->last = 0.0;
-    s->pend_n = 0;
+    s->pend = 0;
 }
 
 // Reduce nvals interleaved partial sums [nblocks][nvals] (fixed order).
@@ -458,35 +490,18 @@ __global__ __launch_bounds__(kThreads) void k_reduce_multi(const double* __restr
 
 constexpr int kVecBlocks = 1024;
 
-// Streamed access (double precision): non-temporal loads and stores, which mark the lines for
-// early eviction.  In double precision one vector of the large grids exceeds the last-level cache
-// anyway, and the update runs at about 6.2 TB/s instead of 5.3; in single precision the r it
-// writes is read again by the next first pass and is better left in the cache.
-template <typename T>
-__device__ __forceinline__ T ld_stream(const T* a)
-{
-    if constexpr (sizeof(T) == 8) return __builtin_nontemporal_load(a);
-    else return *a;
-}
-template <typename T>
-__device__ __forceinline__ void st_stream(T v, T* a)
-{
-    if constexpr (sizeof(T) == 8) __builtin_nontemporal_store(v, a);
-    else *a = v;
-}
-
+// CG's update kernel, for the single-precision loops (in double precision the last pass updates r):
 // x += alpha p (UX; otherwise the next body's first pass applies it), r -= alpha q; returns this
-// thread's part of (r, r).  U grid-strided points per batch, all loads issued before any use (one
-// memory latency per batch); each thread visits its points in increasing order whatever U is, so
-// the sums do not depend on it.
+// thread's part of (r, r).  Four points per batch at the stride of kVecBlocks workgroups, all loads
+// issued before any use (one memory latency per batch).
 template <typename T, bool UX>
 __device__ __forceinline__ double cg_update_loop(long long n, T* __restrict__ x, T* __restrict__ r,
                                                  const T* __restrict__ p, const T* __restrict__ q, T alpha,
-                                                 unsigned bx, unsigned gx)
+                                                 unsigned bx)
 {
-    constexpr int U = (!UX && sizeof(T) == 8) ? 8 : 4;
+    constexpr int U = 4;
     double acc = 0.0;
-    const long long stride = (long long)gx * blockDim.x;
+    const long long stride = (long long)kVecBlocks * blockDim.x;
     long long i = (long long)bx * blockDim.x + threadIdx.x;
     for (; i + (U - 1) * stride < n; i += U * stride) {
         T xv[U], pv[U], rv[U], qv[U];
@@ -494,18 +509,18 @@ __device__ __forceinline__ double cg_update_loop(long long n, T* __restrict__ x,
         for (int u = 0; u < U; u++) {
             const long long j = i + u * stride;
             if (UX) {
-                xv[u] = ld_stream(x + j);
-                pv[u] = ld_stream(p + j);
+                xv[u] = x[j];
+                pv[u] = p[j];
             }
-            rv[u] = ld_stream(r + j);
-            qv[u] = ld_stream(q + j);
+            rv[u] = r[j];
+            qv[u] = q[j];
         }
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const long long j = i + u * stride;
-            if (UX) st_stream(fma(alpha, pv[u], xv[u]), x + j);
+            if (UX) x[j] = fma(alpha, pv[u], xv[u]);
             const T rn = rv[u] - alpha * qv[u];
-            st_stream(rn, r + j);
+            r[j] = rn;
             acc += double(rn) * double(rn);
         }
     }
@@ -518,34 +533,50 @@ __device__ __forceinline__ double cg_update_loop(long long n, T* __restrict__ x,
     return acc;
 }
 
-template <typename T>
-__device__ __forceinline__ void cg_update_body(long long n, T* __restrict__ x, T* __restrict__ r,
-                                               const T* __restrict__ p, const T* __restrict__ q, const Scalars* s,
-                                               double* partials, unsigned bx, unsigned gx)
+// Workgroups of the update that have a point of their own (the others of kVecBlocks would add zero).
+static unsigned update_blocks(long long n)
 {
-    __shared__ double red[kThreads / 64];
+    return (unsigned)std::min<long long>(kVecBlocks, (n + kThreads - 1) / kThreads);
+}
+
+template <typename T>
+__device__ __forceinline__ void cg_update_body(const UpdateArgs<T>& a, unsigned bx)
+{
+    __shared__ double red[2 * kThreads / 64];
+    Scalars* s = a.sc;
+    // alpha from the last pass's partial sums of (q, p), which every workgroup adds up for itself
+    double al = s->alpha;
+    const double qp = sum_partials(a.qp, a.nqp, red);
     if (s->done) return;
-    const T alpha = T(s->alpha);
-    const double acc = x ? cg_update_loop<T, true>(n, x, r, p, q, alpha, bx, gx)
-                         : cg_update_loop<T, false>(n, x, r, p, q, alpha, bx, gx);
+    if (a.nqp) {
+        al = s->rr / qp;
+        if (bx == 0 && threadIdx.x == 0) {
+            s->total = s->qp = qp;
+            s->alpha = al;
+        }
+    }
+    if (a.defer && bx == 0 && threadIdx.x == 0) {
+        s->pend = 1;
+        s->pend_op = RED_CG_END;
+    }
+    const T alpha = T(al);
+    const double acc = a.x ? cg_update_loop<T, true>(a.n, a.x, a.r, a.p, a.q, alpha, bx)
+                           : cg_update_loop<T, false>(a.n, a.x, a.r, a.p, a.q, alpha, bx);
     const double tot = block_sum(acc, red);
-    if (threadIdx.x == 0) partials[bx] = tot;
+    if (threadIdx.x == 0) a.partials[bx] = tot;
 }
 
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_cg_update(long long n, T* __restrict__ x, T* __restrict__ r,
-                                                        const T* __restrict__ p, const T* __restrict__ q,
-                                                        const Scalars* s, double* partials)
+__global__ __launch_bounds__(kThreads) void k_cg_update(UpdateArgs<T> a)
 {
-    cg_update_body<T>(n, x, r, p, q, s, partials, blockIdx.x, gridDim.x);
+    cg_update_body<T>(a, blockIdx.x);
 }
 
-// The CG update of every member of a batch: grid (kVecBlocks, members).
+// The CG update of every member of a batch: grid (workgroups, members).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_cg_update_b(const UpdateArgs<T>* __restrict__ tab)
 {
-    const UpdateArgs<T>& a = tab[blockIdx.y];
-    cg_update_body<T>(a.n, a.x, a.r, a.p, a.q, a.sc, a.partials, blockIdx.x, gridDim.x);
+    cg_update_body<T>(tab[blockIdx.y], blockIdx.x);
 }
 
 // x += alpha p with the loop's last alpha: the update of a CG loop's final body, which the loop
@@ -1009,7 +1040,22 @@ static hipError_t launch_last_ak(const OpPlan& op, const LastArgs<T>& la, int ep
     switch (epi) {
         case EPI_STORE: LAUNCH_LDS((k_last<T, D, AK, EPI_STORE>), dim3(nblk), lds, op.stream, la); break;
         case EPI_RICH: LAUNCH_LDS((k_last<T, D, AK, EPI_RICH>), dim3(nblk), lds, op.stream, la); break;
-        case EPI_CG: LAUNCH_LDS((k_last<T, D, AK, EPI_CG>), dim3(nblk), lds, op.stream, la); break;
+        case EPI_CG:  // CG loops: q and (q, p) in single precision, r and (r, r) in double
+            if constexpr (sizeof(T) == 4) {
+                LAUNCH_LDS((k_last<T, D, AK, EPI_CG>), dim3(nblk), lds, op.stream, la);
+                break;
+            }
+            return hipErrorInvalidValue;
+        case EPI_CGR:
+        case EPI_CGRX:
+            if constexpr (sizeof(T) == 8) {
+                if (epi == EPI_CGR)
+                    LAUNCH_LDS((k_last<T, D, AK, EPI_CGR>), dim3(nblk), lds, op.stream, la);
+                else
+                    LAUNCH_LDS((k_last<T, D, AK, EPI_CGRX>), dim3(nblk), lds, op.stream, la);
+                break;
+            }
+            return hipErrorInvalidValue;
         case EPI_CHEB: LAUNCH_LDS((k_last<T, D, AK, EPI_CHEB>), dim3(nblk), lds, op.stream, la); break;
         case EPI_EM: LAUNCH_LDS((k_last<T, D, AK, EPI_EM>), dim3(nblk), lds, op.stream, la); break;
         default: return hipErrorInvalidValue;
@@ -1047,17 +1093,17 @@ static hipError_t launch_middle(const OpPlan& op, const MidArgs<T>& ma, int mult
     if (op.gen_mid) return gen_middle<T>(op, ma, mult);
     const size_t lds = op.lds_mid;
     if (mult == MULT_G)
-        LAUNCH_LDS((k_middle<T, D, MULT_G>), dim3(ma.ntiles), lds, op.stream, ma);
+        LAUNCH_LDS((k_middle<T, D, MULT_G>), dim3(ma.ntiles + ma.pend.blocks()), lds, op.stream, ma);
     else
-        LAUNCH_LDS((k_middle<T, D, MULT_EM>), dim3(ma.ntiles), lds, op.stream, ma);
+        LAUNCH_LDS((k_middle<T, D, MULT_EM>), dim3(ma.ntiles + ma.pend.blocks()), lds, op.stream, ma);
     return hipGetLastError();
 }
 
 template <typename T>
-static hipError_t launch_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer, int B)
+static hipError_t launch_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int B)
 {
-    if (op.gen_axis) return gen_axis<T>(op, xa, inv, outer, B);
-    dim3 grid(xa.ntiles, outer, op.g.d);
+    if (op.gen_axis) return gen_axis<T>(op, xa, inv, B);
+    const dim3 grid(axis_blocks(xa));
     if (inv)
         LAUNCH_LDS((k_axis<T, true>), grid, op.lds_axis, op.stream, xa);
     else
@@ -1104,7 +1150,15 @@ static hipError_t v2_last(const OpPlan& op, const LastArgs<T>& la, int epi, unsi
     switch (epi) {
         case EPI_STORE: return v2_last_epi<T, D, EPI_STORE>(op, la, nblk);
         case EPI_RICH: return v2_last_epi<T, D, EPI_RICH>(op, la, nblk);
-        case EPI_CG: return v2_last_epi<T, D, EPI_CG>(op, la, nblk);
+        case EPI_CG:
+            if constexpr (sizeof(T) == 4) return v2_last_epi<T, D, EPI_CG>(op, la, nblk);
+            break;
+        case EPI_CGR:
+            if constexpr (sizeof(T) == 8) return v2_last_epi<T, D, EPI_CGR>(op, la, nblk);
+            break;
+        case EPI_CGRX:
+            if constexpr (sizeof(T) == 8) return v2_last_epi<T, D, EPI_CGRX>(op, la, nblk);
+            break;
         case EPI_CHEB: return v2_last_epi<T, D, EPI_CHEB>(op, la, nblk);
         case EPI_EM: return v2_last_epi<T, D, EPI_EM>(op, la, nblk);
     }
@@ -1145,9 +1199,9 @@ static hipError_t v2_middle(const OpPlan& op, const MidArgs<T>& ma, int mult)
 #define C(LL, A1, A2)                                                                          \
     case LL:                                                                                   \
         if (mult == MULT_G)                                                                    \
-            LAUNCH_LDS((k2_middle<T, D, A1, A2, MULT_G>), dim3(ma.ntiles), lds, op.stream, ma);  \
+            LAUNCH_LDS((k2_middle<T, D, A1, A2, MULT_G>), dim3(ma.ntiles + ma.pend.blocks()), lds, op.stream, ma);  \
         else                                                                                   \
-            LAUNCH_LDS((k2_middle<T, D, A1, A2, MULT_EM>), dim3(ma.ntiles), lds, op.stream, ma); \
+            LAUNCH_LDS((k2_middle<T, D, A1, A2, MULT_EM>), dim3(ma.ntiles + ma.pend.blocks()), lds, op.stream, ma); \
         break;
         V2_COL_CASES(C)
 #undef C
@@ -1157,9 +1211,9 @@ static hipError_t v2_middle(const OpPlan& op, const MidArgs<T>& ma, int mult)
 }
 
 template <typename T>
-static hipError_t v2_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer, int B)
+static hipError_t v2_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int B)
 {
-    dim3 grid(xa.ntiles, outer, op.g.d);
+    const dim3 grid(axis_blocks(xa));
     const size_t lds = op.lds_axis;
     switch (xa.ax.L) {
 #define C(LL, A1, A2)                                                                        \
@@ -1229,10 +1283,10 @@ static hipError_t v2_last_b(const OpPlan& op, const LastArgs<T>* tab, int epi, b
 }
 
 template <typename T, int D>
-static hipError_t v2_middle_b(const OpPlan& op, const MidArgs<T>* tab, int mult, int ntiles, int nb)
+static hipError_t v2_middle_b(const OpPlan& op, const MidArgs<T>* tab, int mult, int blocks, int nb)
 {
     const size_t lds = op.lds_mid;
-    const dim3 grid(ntiles, nb);
+    const dim3 grid(blocks, nb);
     switch (op.ax[0].L) {
 #define C(LL, A1, A2)                                                                          \
     case LL:                                                                                   \
@@ -1249,17 +1303,17 @@ static hipError_t v2_middle_b(const OpPlan& op, const MidArgs<T>* tab, int mult,
 }
 
 template <typename T>
-static hipError_t v2_axis_b(const OpPlan& op, const AxisArgs<T>* tab, bool inv, int ntiles, int outer, int B, int nb)
+static hipError_t v2_axis_b(const OpPlan& op, const AxisArgs<T>* tab, bool inv, int blocks, int B, int nb)
 {
-    const dim3 grid(ntiles, outer, op.g.d * nb);
+    const dim3 grid(blocks, nb);
     const size_t lds = op.lds_axis;
     switch (op.ax[1].L) {
 #define C(LL, A1, A2)                                                                           \
     case LL:                                                                                    \
         if (inv)                                                                                \
-            LAUNCH_LDS((k2_axis_b<T, A1, A2, true>), grid, lds, op.stream, tab, B, op.g.d);     \
+            LAUNCH_LDS((k2_axis_b<T, A1, A2, true>), grid, lds, op.stream, tab, B);     \
         else                                                                                    \
-            LAUNCH_LDS((k2_axis_b<T, A1, A2, false>), grid, lds, op.stream, tab, B, op.g.d);    \
+            LAUNCH_LDS((k2_axis_b<T, A1, A2, false>), grid, lds, op.stream, tab, B);    \
         break;
         V2_COL_CASES(C)
 #undef C
@@ -1286,6 +1340,7 @@ static MidArgs<T> mid_args(const OpPlan& op, cpx<T>* buf, const int* done)
     ma.buf = buf;
     ma.twg = static_cast<const cpx<T>*>(op.tw[0]);
     ma.done = done;
+    ma.pend = Pending{};
     return ma;
 }
 
@@ -1316,6 +1371,16 @@ static hipError_t build_bundle_d(const OpPlan& op, const ApplyArgs& a, ApplyBund
     fa.r = static_cast<const T*>(a.r_cg);
     fa.xd = static_cast<T*>(a.x_cg);
     fa.sc = op.sc;
+    fa.end_part = a.op == OP_AP_CG && a.defer_redop >= 0 ? a.end_part : nullptr;
+    fa.pq_part = a.cg_pq ? op.partials2 : nullptr;
+    // what the pass after the first one completes: the previous body's end, and CG's alpha
+    const bool fused = a.next_op >= 0;
+    const int rpb_last = fused ? op.rpb_fused : op.rpb;
+    bu->nblk_last = (unsigned)((g.rows + rpb_last - 1) / rpb_last);
+    const int nend = a.defer_redop < 0 ? 0 : a.nend ? a.nend : (int)bu->nblk_last;
+    fa.nend = nend;
+    const Pending pend = {a.defer_redop >= 0 || a.cg_pq == 2 ? op.sc : nullptr, a.end_part, op.partials2, nend,
+                          a.cg_pq == 2 ? (int)bu->nblk1 : 0};
     const int* done = a.loop ? &op.sc->done : nullptr;
     fa.done = done;
     for (int c = 0; c < 3; c++) fa.E[c] = a.E[c];
@@ -1343,9 +1408,9 @@ static hipError_t build_bundle_d(const OpPlan& op, const ApplyArgs& a, ApplyBund
         xa.out = SB;
         xa.twg = static_cast<const cpx<T>*>(op.tw[1]);
         xa.done = done;
-        // the previous body's deferred loop reduction is completed by this pass's first workgroup
-        xa.red_sc = a.defer_redop >= 0 ? op.sc : nullptr;
-        xa.partials = op.partials;
+        xa.outer = g.L[0];
+        xa.comps = D;
+        xa.pend = pend;
         mid = SB;
         AxisArgs<T>& xi = bu->xi;
         xi.ax = op.ax[1];
@@ -1364,8 +1429,11 @@ static hipError_t build_bundle_d(const OpPlan& op, const ApplyArgs& a, ApplyBund
         xi.out = SA;
         xi.twg = static_cast<const cpx<T>*>(op.tw[1]);
         xi.done = done;
+        xi.outer = g.L[0];
+        xi.comps = D;
     }
     bu->ma = mid_args<T>(op, mid, done);
+    if (D == 2) bu->ma.pend = pend;
 
     LastArgs<T>& la = bu->la;
     la.g = g;
@@ -1388,23 +1456,17 @@ static hipError_t build_bundle_d(const OpPlan& op, const ApplyArgs& a, ApplyBund
     la.partials = op.partials;
     la.twg = static_cast<const cpx<T>*>(op.tw[last]);
     la.done = done;
-    la.sc = a.cheb_dev ? op.sc : nullptr;
+    la.sc = a.cheb_dev || a.epi == EPI_CGR || a.epi == EPI_CGRX ? op.sc : nullptr;
     la.out = SA;
-    if (a.defer_redop >= 0 && !(D == 3 && op.v2_axis && op.v2_row)) return hipErrorInvalidValue;
-    la.defer_sc = a.defer_redop >= 0 ? op.sc : nullptr;
+    // (with a CG update kernel the pending end is that kernel's)
+    la.defer_sc = a.defer_redop >= 0 && a.epi != EPI_CG ? op.sc : nullptr;
     la.redop = a.defer_redop;
-    const bool fused = a.next_op >= 0;
     if (fused && (!fusable(op) || a.next_op != (a.epi == EPI_EM ? OP_EM : OP_AX) ||
                   (a.epi != EPI_RICH && a.epi != EPI_CHEB && a.epi != EPI_EM)))
         return hipErrorInvalidValue;
     bu->fused = fused;
-    bu->nblk_last = (unsigned)((g.rows + op.rpb - 1) / op.rpb);
-    if (fused) {
-        // the fused pass has its own (tuned, even) rows per block
-        la.rpb = op.rpb_fused;
-        la.npen = (op.rpb_fused * D + 1) / 2;
-        bu->nblk_last = (unsigned)((g.rows + op.rpb_fused - 1) / op.rpb_fused);
-    }
+    la.rpb = rpb_last;  // the fused pass has its own (tuned, even) rows per block
+    la.npen = (rpb_last * D + 1) / 2;
     return hipSuccess;
 }
 
@@ -1422,12 +1484,13 @@ static hipError_t apply_d(const OpPlan& op, const ApplyArgs& a, int* nblocks_las
             hipSuccess)
             return e;
         if (prof_PK_FIRST && (e = op.prof->end()) != hipSuccess) return e;
+        if (a.cg_pq == 1 && (e = run_reduce_async(op, (int)bu.nblk1, RED_CG_ALPHA, op.partials2)) != hipSuccess) return e;
     }
     if (a.first_only) return hipSuccess;
     if (D == 3) {
         const bool prof_PK_AXIS_FWD = op.prof && op.prof->wants(PK_AXIS_FWD);
         if (prof_PK_AXIS_FWD && (e = op.prof->begin(PK_AXIS_FWD)) != hipSuccess) return e;
-        if ((e = op.v2_axis ? v2_axis<T>(op, bu.xf, false, g.L[0], g.B[1]) : launch_axis<T>(op, bu.xf, false, g.L[0], g.B[1])) !=
+        if ((e = op.v2_axis ? v2_axis<T>(op, bu.xf, false, g.B[1]) : launch_axis<T>(op, bu.xf, false, g.B[1])) !=
             hipSuccess)
             return e;
         if (prof_PK_AXIS_FWD && (e = op.prof->end()) != hipSuccess) return e;
@@ -1440,7 +1503,7 @@ static hipError_t apply_d(const OpPlan& op, const ApplyArgs& a, int* nblocks_las
     if (D == 3) {
         const bool prof_PK_AXIS_INV = op.prof && op.prof->wants(PK_AXIS_INV);
         if (prof_PK_AXIS_INV && (e = op.prof->begin(PK_AXIS_INV)) != hipSuccess) return e;
-        if ((e = op.v2_axis ? v2_axis<T>(op, bu.xi, true, g.L[0], g.B[1]) : launch_axis<T>(op, bu.xi, true, g.L[0], g.B[1])) !=
+        if ((e = op.v2_axis ? v2_axis<T>(op, bu.xi, true, g.B[1]) : launch_axis<T>(op, bu.xi, true, g.B[1])) !=
             hipSuccess)
             return e;
         if (prof_PK_AXIS_INV && (e = op.prof->end()) != hipSuccess) return e;
@@ -1490,7 +1553,9 @@ hipError_t run_axis_only(const OpPlan& op)
     xa.out = static_cast<cpx<T>*>(op.SB);
     xa.twg = static_cast<const cpx<T>*>(op.tw[1]);
     xa.done = nullptr;
-    return op.v2_axis ? v2_axis<T>(op, xa, false, g.L[0], g.B[1]) : launch_axis<T>(op, xa, false, g.L[0], g.B[1]);
+    xa.outer = g.L[0];
+    xa.comps = 3;
+    return op.v2_axis ? v2_axis<T>(op, xa, false, g.B[1]) : launch_axis<T>(op, xa, false, g.B[1]);
 }
 template hipError_t run_axis_only<double>(const OpPlan&);
 template hipError_t run_axis_only<float>(const OpPlan&);
@@ -1534,6 +1599,7 @@ hipError_t run_first_cg_only(const OpPlan& op, T* x, const T* r, T* p)
     fa.A = op.A;
     fa.out = static_cast<cpx<T>*>(op.SA);
     fa.twg = static_cast<const cpx<T>*>(op.tw[d - 1]);
+    fa.pq_part = sizeof(T) == 8 ? op.partials2 : nullptr;
     const unsigned nblk = (unsigned)((g.rows + op.rpb_first_x - 1) / op.rpb_first_x);
     return d == 2 ? v2_first<T, 2>(op, fa, OP_AP_CG, nblk) : v2_first<T, 3>(op, fa, OP_AP_CG, nblk);
 }
@@ -1603,7 +1669,9 @@ static hipError_t axis_custom(const OpPlan& op, const Axis& ax, const void* tw, 
     xa.in = reinterpret_cast<const cpx<double>*>(in);
     xa.out = reinterpret_cast<cpx<double>*>(out);
     xa.twg = static_cast<const cpx<double>*>(tw);
-    return launch_axis<double>(o, xa, inv, outer, bin ? nin : bout ? nout : ax.L);
+    xa.outer = outer;
+    xa.comps = op.g.d;
+    return launch_axis<double>(o, xa, inv, bin ? nin : bout ? nout : ax.L);
 }
 
 hipError_t run_prolong(const OpPlan& opn, const OpPlan& opm, const double* xn, double* ym)
@@ -1742,9 +1810,9 @@ static hipError_t apply_batch_d(const OpPlan& op, const ApplyBundle<T>& b0, cons
     hipError_t e;
     if (!b0.skip_first && (e = v2_first_b<T, D>(op, t.fa, b0.op, b0.nblk1, nb)) != hipSuccess) return e;
     if (b0.first_only) return hipSuccess;
-    if (D == 3 && (e = v2_axis_b<T>(op, t.xf, false, b0.xf.ntiles, g.L[0], g.B[1], nb)) != hipSuccess) return e;
-    if ((e = v2_middle_b<T, D>(op, t.ma, b0.mult, b0.ma.ntiles, nb)) != hipSuccess) return e;
-    if (D == 3 && (e = v2_axis_b<T>(op, t.xi, true, b0.xi.ntiles, g.L[0], g.B[1], nb)) != hipSuccess) return e;
+    if (D == 3 && (e = v2_axis_b<T>(op, t.xf, false, axis_blocks(b0.xf), g.B[1], nb)) != hipSuccess) return e;
+    if ((e = v2_middle_b<T, D>(op, t.ma, b0.mult, b0.ma.ntiles + b0.ma.pend.blocks(), nb)) != hipSuccess) return e;
+    if (D == 3 && (e = v2_axis_b<T>(op, t.xi, true, axis_blocks(b0.xi), g.B[1], nb)) != hipSuccess) return e;
     return v2_last_b<T, D>(op, t.la, b0.epi, b0.fused, b0.nblk_last, nb);
 }
 
@@ -1763,12 +1831,12 @@ hipError_t run_reduce_batch(hipStream_t s, const ReduceArgs* tab, int nb, int re
 }
 
 template <typename T>
-hipError_t run_cg_update_batch(hipStream_t s, const UpdateArgs<T>* tab, int nb)
+hipError_t run_cg_update_batch(hipStream_t s, const UpdateArgs<T>* tab, long long n, int nb)
 {
-    hipLaunchKernelGGL(k_cg_update_b<T>, dim3(kVecBlocks, nb), dim3(kThreads), 0, s, tab);
+    hipLaunchKernelGGL(k_cg_update_b<T>, dim3(update_blocks(n), nb), dim3(kThreads), 0, s, tab);
     return hipGetLastError();
 }
-template hipError_t run_cg_update_batch<float>(hipStream_t, const UpdateArgs<float>*, int);
+template hipError_t run_cg_update_batch<float>(hipStream_t, const UpdateArgs<float>*, long long, int);
 
 
 hipError_t run_init_loop(const OpPlan& op, double rr, double alpha, double beta, double thr, double npts,
@@ -1803,9 +1871,9 @@ hipError_t run_set_scalar(const OpPlan& op, double* dst, double v)
         }                                                                                       \
     } while (0)
 
-hipError_t run_reduce_async(const OpPlan& op, int n, int redop)
+hipError_t run_reduce_async(const OpPlan& op, int n, int redop, const double* partials)
 {
-    LAUNCH_TIMED(PK_REDUCE, op, k_reduce, dim3(1), op.stream, op.partials, n, op.sc, redop);
+    LAUNCH_TIMED(PK_REDUCE, op, k_reduce, dim3(1), op.stream, partials ? partials : op.partials, n, op.sc, redop);
     return hipGetLastError();
 }
 
@@ -1819,14 +1887,15 @@ hipError_t run_reduce(const OpPlan& op, int n, int redop, double* host_out)
     return hipStreamSynchronize(op.stream);
 }
 
+int cg_update_blocks(long long n) { return (int)update_blocks(n); }
+
 template <typename T>
-hipError_t run_cg_update(const OpPlan& op, long long n, T* x, T* r, const T* p, const T* q)
+hipError_t run_cg_update(const OpPlan& op, const UpdateArgs<T>& a)
 {
-    LAUNCH_TIMED(PK_CG_UPDATE, op, k_cg_update<T>, dim3(kVecBlocks), op.stream, n, x, r, p, q, op.sc, op.partials);
+    LAUNCH_TIMED(PK_CG_UPDATE, op, k_cg_update<T>, dim3(update_blocks(a.n)), op.stream, a);
     return hipGetLastError();
 }
-template hipError_t run_cg_update<float>(const OpPlan&, long long, float*, float*, const float*, const float*);
-template hipError_t run_cg_update<double>(const OpPlan&, long long, double*, double*, const double*, const double*);
+template hipError_t run_cg_update<float>(const OpPlan&, const UpdateArgs<float>&);
 
 template <typename T>
 hipError_t run_cg_x(const OpPlan& op, long long n, T* x, const T* p)

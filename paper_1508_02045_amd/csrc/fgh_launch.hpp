@@ -71,6 +71,7 @@ struct OpPlan {
     bool gen_row, gen_axis, gen_mid;
     int th_row, th_axis, th_mid, ni_row, ni_axis, ni_mid;
     double* partials;        // one double per block of the last pass (and of vector kernels)
+    double* partials2;       // CG: one per block of the first pass (A p, p) or of the update (r, r)
     Scalars* sc;
     hipStream_t stream;
     Profiler* prof = nullptr;  // non-null while profiling is enabled
@@ -102,11 +103,24 @@ struct ApplyArgs {
     int next_op = -1;
     bool skip_first = false;
     bool first_only = false;
-    // >= 0 (3D, specialised row and axis kernels): the loop reduction (RedOp) of this body's last
-    // pass is left to the first workgroup of the next body's forward axis pass, which replaces
-    // the separate single-block reduction launch
+    // >= 0: the loop reduction (RedOp) that ends this body is left to a workgroup of the pass after
+    // the next body's first pass (the strided pass in 3D, the middle pass in 2D), which replaces
+    // the separate single-block reduction launch; end_part, nend: its partial sums (nend = 0: one
+    // per block of this body's last pass)
     int defer_redop = -1;
+    const double* end_part = nullptr;
+    int nend = 0;
+    // CG in double precision: the first pass leaves the partial sums of (A p, p); alpha is completed
+    // by a reduction launch of its own (1) or by a workgroup of the pass after it (2)
+    int cg_pq = 0;
 };
+
+// Workgroups of a strided pass: its tiles and those of the pending loop reductions.
+template <typename T>
+inline unsigned axis_blocks(const AxisArgs<T>& a)
+{
+    return (unsigned)((long long)a.ntiles * a.outer * a.comps + a.pend.blocks());
+}
 
 // Tile of a run-time-length pass: rows per block or columns per tile, threads, dense products per
 // wavefront and LDS bytes; ok = false where the mixed-radix passes are used.
@@ -124,7 +138,7 @@ hipError_t gen_first(const OpPlan& op, const FirstArgs<T>& fa, int opc, unsigned
 template <typename T>
 hipError_t gen_last(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned nblk);
 template <typename T>
-hipError_t gen_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int outer, int B);
+hipError_t gen_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int B);
 template <typename T>
 hipError_t gen_middle(const OpPlan& op, const MidArgs<T>& ma, int mult);
 
@@ -165,8 +179,11 @@ struct UpdateArgs {
     T* r;
     const T* p;
     const T* q;
-    const Scalars* sc;
+    Scalars* sc;
     double* partials;
+    const double* qp;  // nqp partial sums of (q, p) that alpha is taken from (nqp = 0: from sc)
+    int nqp;
+    int defer;         // the body's end is left pending (its partial sums are this kernel's)
 };
 // Device tables of a batch of up to kMaxBatch members, carved out of a device region of
 // kBatchSlabBytes (struct-of-arrays: the argument blocks of one kind are contiguous).
@@ -197,7 +214,7 @@ template <typename T>
 hipError_t run_apply_batch(const OpPlan& op0, const ApplyBundle<T>& b0, const BatchTables<T>& t, int nb);
 hipError_t run_reduce_batch(hipStream_t s, const ReduceArgs* tab, int nb, int redop);
 template <typename T>
-hipError_t run_cg_update_batch(hipStream_t s, const UpdateArgs<T>* tab, int nb);
+hipError_t run_cg_update_batch(hipStream_t s, const UpdateArgs<T>* tab, long long n, int nb);
 
 hipError_t run_reduce(const OpPlan& op, int n, int redop, double* host_out);
 
@@ -224,14 +241,15 @@ hipError_t run_fused_only(const OpPlan& op, T* x);
 // Trigonometric prolongation of a real vector field from the N grid of `opn` to the 2N-1 grid of
 // `opm` (both double precision; opm's spectrum buffers are used as scratch).
 hipError_t run_prolong(const OpPlan& opn, const OpPlan& opm, const double* xn, double* ym);
-hipError_t run_reduce_async(const OpPlan& op, int n, int redop);
+hipError_t run_reduce_async(const OpPlan& op, int n, int redop, const double* partials = nullptr);
 hipError_t run_set_scalar(const OpPlan& op, double* dst, double v);
 hipError_t run_init_loop(const OpPlan& op, double rr, double alpha, double beta, double thr, double npts,
                          double blowup, double cheb_c, double cheb_delta, int limit);
 
 int vec_blocks();
+int cg_update_blocks(long long n);  // workgroups (and partial sums) of CG's update kernel
 template <typename T>
-hipError_t run_cg_update(const OpPlan& op, long long n, T* x, T* r, const T* p, const T* q);
+hipError_t run_cg_update(const OpPlan& op, const UpdateArgs<T>& a);
 template <typename T>
 hipError_t run_cg_x(const OpPlan& op, long long n, T* x, const T* p);
 // CG's first pass with the deferred iterate update alone (tile timing): x += alpha p,

@@ -33,17 +33,22 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// What ends a loop whose stopping-test value (raw sum) is v after its next body: 0 nothing, else
+// Scalars::done.
+__device__ __forceinline__ int end_state(const Scalars* s, double v)
+{
+    const double q = sqrt(v / s->npts);
+    if (!(v == v) || v > 1.0e300 || (s->blowup > 0.0 && q > s->blowup)) return 3;
+    if (s->thr >= 0.0 && q <= s->thr) return 1;
+    return s->m + 1 >= s->limit ? 2 : 0;
+}
+
 __device__ __forceinline__ void end_body(Scalars* s, double v)
 {
+    const int d = end_state(s, v);
     s->m += 1;
-    const double q = sqrt(v / s->npts);
-    s->last = q;
-    if (!(v == v) || v > 1.0e300 || (s->blowup > 0.0 && q > s->blowup))
-        s->done = 3;
-    else if (s->thr >= 0.0 && q <= s->thr)
-        s->done = 1;
-    else if (s->m >= s->limit)
-        s->done = 2;
+    s->last = sqrt(v / s->npts);
+    if (d) s->done = d;
 }
 
 // The scalar update that ends a loop reduction (RedOp) from its total.
@@ -71,37 +76,103 @@ __device__ __forceinline__ void apply_redop(Scalars* s, int op, double tot)
     }
 }
 
-// This thread's share of n partial sums, in index order (thread t sums t, t + blockDim, ...);
-// loads are issued eight at a time so that one memory latency covers eight of them.
-__device__ __forceinline__ double sum_partials(const double* partials, int n)
+// Sums of two arrays of partial sums (na and nb of them, 0 allowed), the same in every thread and
+// whatever the workgroup's size: the order is that of kThreads threads (thread t sums t,
+// t + kThreads, ...), each wavefront's shuffle tree, then the wavefronts in turn.  Loads are issued
+// eight at a time, and both arrays' first ones together, so that one memory latency covers them.
+// All threads of the workgroup call it; red: 2 kThreads / 64 doubles of LDS that are free on entry.
+__device__ __forceinline__ double partial_share(const double* p, int n, int i)
 {
     double v = 0.0;
-    const int bd = (int)blockDim.x;
-    int i = threadIdx.x;
-    for (; i + 7 * bd < n; i += 8 * bd) {
+    for (; i + 7 * kThreads < n; i += 8 * kThreads) {
         double t[8];
 #pragma unroll
-        for (int u = 0; u < 8; u++) t[u] = partials[i + u * bd];
+        for (int u = 0; u < 8; u++) t[u] = p[i + u * kThreads];
 #pragma unroll
         for (int u = 0; u < 8; u++) v += t[u];
     }
-    for (; i < n; i += bd) v += partials[i];
+    if (i < n) {
+        double t[7];
+#pragma unroll
+        for (int u = 0; u < 7; u++) t[u] = i + u * kThreads < n ? p[i + u * kThreads] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 7; u++)
+            if (i + u * kThreads < n) v += t[u];
+    }
     return v;
 }
-
-// A loop reduction deferred by the last pass of the previous body (Scalars::pend_n partial sums)
-// is completed by the first workgroup of the next body's first kernel: the partials were written
-// by an earlier kernel, so no fence or counter is needed.  Same summation order and scalar update
-// as the separate reduction kernel.  All threads of the workgroup call this.
-__device__ __forceinline__ void finish_deferred(Scalars* s, const double* partials, double* red)
+__device__ __forceinline__ void sum_partials2(const double* a, int na, const double* b, int nb, double* red,
+                                              double* sa, double* sb)
 {
-    const int n = s->pend_n;
-    if (n == 0) return;
-    const double tot = block_sum(sum_partials(partials, n), red);
-    if (threadIdx.x == 0) {
-        apply_redop(s, s->pend_op, tot);
-        s->pend_n = 0;
+    constexpr int W = kThreads / 64;
+    const int lane = threadIdx.x & 63, nw = (int)blockDim.x >> 6;
+    for (int w = (int)threadIdx.x >> 6; w < W; w += nw) {
+        double va = partial_share(a, na, w * 64 + lane), vb = partial_share(b, nb, w * 64 + lane);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            va += __shfl_down(va, off, 64);
+            vb += __shfl_down(vb, off, 64);
+        }
+        if (lane == 0) {
+            red[w] = va;
+            red[W + w] = vb;
+        }
     }
+    __syncthreads();
+    *sa = *sb = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; w++) {
+        *sa += red[w];
+        *sb += red[W + w];
+    }
+}
+__device__ __forceinline__ double sum_partials(const double* p, int n, double* red)
+{
+    double s, none;
+    sum_partials2(p, n, p, 0, red, &s, &none);
+    return s;
+}
+
+// Completes the pending loop reductions in their own workgroup (b < Pending::kBlocks of the launch;
+// the first does it).  The partial sums were written by
+// earlier kernels, so no fence or counter is needed.  Same summation order and scalar update as
+// the separate reduction kernel.  The sums are taken whether or not an end is pending, so that their
+// loads do not wait for the flag.
+__device__ __forceinline__ void finish_pending(const Pending& p, int b)
+{
+    if (b) return;
+    __shared__ double red[2 * kThreads / 64];
+    Scalars* s = p.sc;
+    double end, pq;
+    sum_partials2(p.end, p.nend, p.pq, p.npq, red, &end, &pq);
+    if (threadIdx.x == 0) {
+        if (s->pend) {
+            apply_redop(s, s->pend_op, end);
+            s->pend = 0;
+        }
+        if (p.npq && !s->done) apply_redop(s, RED_CG_ALPHA, pq);
+    }
+}
+
+// CG's beta for the first pass: from the scalar block, or, while the previous body's end is
+// pending, from the partial sums of its (r, r), which every workgroup adds up for itself.  Returns
+// false where the loop has stopped or that end stops it (the next kernel records it): nothing is
+// to be done then.
+template <typename T>
+__device__ __forceinline__ bool first_beta(const FirstArgs<T>& a, double* red, T* beta)
+{
+    const Scalars* s = a.sc;
+    double b = s->beta;
+    if (a.end_part) {  // the sums' loads do not wait for the flags
+        const double tot = sum_partials(a.end_part, a.nend, red);
+        if (*a.done) return false;
+        if (s->pend) {
+            if (end_state(s, tot)) return false;
+            b = tot / s->rr;
+        }
+    }
+    *beta = T(b);
+    return true;
 }
 
 constexpr int smallest_factor(int n)
@@ -268,9 +339,12 @@ struct RowLen {
 // Stage 0 of the first pass for KU points starting at this thread's index base + threadIdx.x:
 // z = A(pt) u with u per FirstOp.  Real rows 2m and 2m + 1 of the tile (row r, component c:
 // r D + c) are written as the real and imaginary parts of complex row m (RS slots apart).
+// For CG's operand in double precision this thread's part of (A p, p) is added to acc (point by point,
+// so that it does not depend on KU).
 template <typename T, int D, int LT, int KU, bool XD = false>
 __device__ __forceinline__ void first_stage0_chunk(const FirstArgs<T>& a, int op, const T* tab, T beta, int base,
-                                                   int total, int lim, long long pt0, T* Zr, RowLen<LT> rl, int RS)
+                                                   int total, int lim, long long pt0, T* Zr, RowLen<LT> rl, int RS,
+                                                   double& acc)
 {
     const unsigned npts = (unsigned)a.g.npts;  // 32-bit offsets: d |grid| < 2^31 here
     unsigned pt[KU];
@@ -365,6 +439,13 @@ __device__ __forceinline__ void first_stage0_chunk(const FirstArgs<T>& a, int op
 #pragma unroll
             for (int c = 0; c < D; c++) z[u][c] -= T(a.omega) * uu[u][c];
     }
+    if (sizeof(T) == 8 && op == OP_AP_CG) {
+#pragma unroll
+        for (int u = 0; u < KU; u++)
+#pragma unroll
+            for (int c = 0; c < D; c++)
+                if (ok[u]) acc += double(z[u][c]) * double(uu[u][c]);
+    }
 #pragma unroll
     for (int u = 0; u < KU; u++) {
         const int idx = base + u * (int)blockDim.x + (int)threadIdx.x;
@@ -380,10 +461,35 @@ __device__ __forceinline__ void first_stage0_chunk(const FirstArgs<T>& a, int op
     }
 }
 
+// The twiddle table of a length on its way to LDS: load() early, store() once other loads are under
+// way, so that the two share one memory latency.  (kThreads threads.)
+template <typename T, int L>
+struct TwiddleCopy {
+    static constexpr int N = (L + kThreads - 1) / kThreads;
+    cpx<T> v[N];
+    __device__ __forceinline__ void load(const cpx<T>* g)
+    {
+#pragma unroll
+        for (int u = 0; u < N; u++) {
+            const int m = (int)threadIdx.x + u * kThreads;
+            v[u] = g[m < L ? m : 0];
+        }
+    }
+    __device__ __forceinline__ void store(cpx<T>* tw) const
+    {
+#pragma unroll
+        for (int u = 0; u < N; u++) {
+            const int m = (int)threadIdx.x + u * kThreads;
+            if (m < L) tw[m] = v[u];
+        }
+    }
+};
+
 // Epilogue of the last pass for kU points: y from the real rows Zr, the solver update per Epi.
 template <typename T, int D, int LT, int epi, int KU>
 __device__ __forceinline__ double last_epilogue_chunk(const LastArgs<T>& a, const T* tabinv, int base, int total,
-                                                      int lim, long long pt0, const T* Zr, RowLen<LT> rl, int RS)
+                                                      int lim, long long pt0, const T* Zr, RowLen<LT> rl, int RS,
+                                                      double acc = 0.0)
 {
     const unsigned npts = (unsigned)a.g.npts;  // 32-bit offsets: d |grid| < 2^31 here
     unsigned pt[KU];
@@ -404,7 +510,6 @@ __device__ __forceinline__ double last_epilogue_chunk(const LastArgs<T>& a, cons
             y[u][c] = Zr[((q >> 1) * RS + i) * 2 + (q & 1)];
         }
     }
-    double acc = 0.0;
     if constexpr (epi == EPI_STORE) {
         const T sg = T(a.sgn);
 #pragma unroll
@@ -448,6 +553,38 @@ __device__ __forceinline__ double last_epilogue_chunk(const LastArgs<T>& a, cons
                     comp(a.q, c, npts)[pt[u]] = y[u][c];
                     acc += double(y[u][c]) * double(pv[u][c]);
                 }
+    } else if constexpr (epi == EPI_CGR || epi == EPI_CGRX) {
+        T rv[KU][D];
+#pragma unroll
+        for (int u = 0; u < KU; u++)
+#pragma unroll
+            for (int c = 0; c < D; c++) rv[u][c] = comp(a.r, c, npts)[pt[u]];
+        const T al = T(a.sc->alpha);
+        if constexpr (epi == EPI_CGRX) {
+            T xv[KU][D], pv[KU][D];
+#pragma unroll
+            for (int u = 0; u < KU; u++)
+#pragma unroll
+                for (int c = 0; c < D; c++) {
+                    xv[u][c] = comp(a.x, c, npts)[pt[u]];
+                    pv[u][c] = comp(a.p, c, npts)[pt[u]];
+                }
+#pragma unroll
+            for (int u = 0; u < KU; u++)
+#pragma unroll
+                for (int c = 0; c < D; c++)
+                    if (ok[u]) comp(a.x, c, npts)[pt[u]] = fma(al, pv[u][c], xv[u][c]);
+        }
+#pragma unroll
+        for (int u = 0; u < KU; u++)
+#pragma unroll
+            for (int c = 0; c < D; c++) {
+                const T rn = rv[u][c] - al * y[u][c];
+                if (ok[u]) {
+                    comp(a.r, c, npts)[pt[u]] = rn;
+                    acc += double(rn) * double(rn);
+                }
+            }
     } else if constexpr (epi == EPI_CHEB) {
         T xv[KU][D], rv[KU][D], pv[KU][D];
 #pragma unroll
@@ -660,37 +797,45 @@ __device__ __forceinline__ void first_transform_store_ip(const Args& a, long lon
 // First pass with one LDS buffer of npairs packed rows (the stages run in place).
 // LDS: twiddles | Zc (npairs complex rows) | phase table.
 template <typename T, int D, int L1, int L2, int KU = FirstTune<T, L1 * L2>::ku, int KX = FirstTune<T, L1 * L2>::kx>
-__device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, long long b, long long nb)
+__device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, int b, int nb)
 {
-    if (a.done && *a.done) return;
+    if (!a.end_part && a.done && *a.done) return;
     constexpr int L = L1 * L2;
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[2 * kThreads / 64];
     const int npairs = (a.rpb * D + 1) / 2;
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* Zc = tw + L;
     T* tab = reinterpret_cast<T*>(Zc + npairs * L);
-    for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
+    TwiddleCopy<T, L> tc;
+    tc.load(a.twg);
     if (a.A.kind == AK_PHASE)
         for (int m = threadIdx.x; m < kMaxPhases * 6; m += blockDim.x) tab[m] = T(a.A.tab[m / 6][m % 6]);
+    tc.store(tw);
     if ((a.rpb * D) & 1)  // the imaginary half of the last packed row is a zero row
         for (int i = threadIdx.x; i < L; i += blockDim.x) Zc[(npairs - 1) * L + i].y = T(0);
+    T beta = T(0);
+    if (op == OP_AP_CG && !first_beta(a, red, &beta)) return;
     lds_barrier();
     const long long row0 = xcd_tile(b, nb) * a.rpb;
-    const T beta = (op == OP_AP_CG) ? T(a.sc->beta) : T(0);
+    double acc = 0.0;
     {
         const int total = a.rpb * L;
         const long long pt0 = row0 * L;
         const long long left = a.g.rows * (long long)L - pt0;
         const int lim = left < total ? (int)left : total;
+        T* Zr = reinterpret_cast<T*>(Zc);
         if (op == OP_AP_CG && a.xd) {
             for (int base = 0; base < total; base += KX * blockDim.x)
-                first_stage0_chunk<T, D, L, KX, true>(a, op, tab, beta, base, total, lim, pt0,
-                                                      reinterpret_cast<T*>(Zc), RowLen<L>{}, L);
+                first_stage0_chunk<T, D, L, KX, true>(a, op, tab, beta, base, total, lim, pt0, Zr, RowLen<L>{}, L, acc);
         } else {
             for (int base = 0; base < total; base += KU * blockDim.x)
-                first_stage0_chunk<T, D, L, KU>(a, op, tab, beta, base, total, lim, pt0,
-                                                reinterpret_cast<T*>(Zc), RowLen<L>{}, L);
+                first_stage0_chunk<T, D, L, KU>(a, op, tab, beta, base, total, lim, pt0, Zr, RowLen<L>{}, L, acc);
         }
+    }
+    if (sizeof(T) == 8 && a.pq_part) {
+        const double tot = block_sum(acc, red);
+        if (threadIdx.x == 0) a.pq_part[b] = tot;
     }
     lds_barrier();
     first_transform_store_ip<T, D, L1, L2>(a, row0, tw, Zc);
@@ -711,55 +856,80 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     first_body<T, D, L1, L2>(tab[blockIdx.y], op, blockIdx.x, gridDim.x);
 }
 
+// Step-A jobs of a strided or middle pass: load a subsequence and transform it, then write it to LDS
+// times its twiddles; table() puts those there.  A thread's first job runs up to its twiddles ahead
+// of the table's barrier, so that the pass starts with one memory latency instead of two (243^3:
+// strided passes 173 and 157 -> 158 and 140 us).  The loads stay in one block with the transform:
+// apart from it the compiler contracts other products, and refined solves keep their rounding.
+template <typename FT, typename FL, typename FX>
+__device__ __forceinline__ void run_jobs(int n, FT table, FL load_transform, FX write)
+{
+    int job = threadIdx.x;
+    if (job < n) load_transform(job);
+    table();
+    lds_barrier();
+    while (job < n) {
+        write();
+        job += blockDim.x;
+        if (job < n) load_transform(job);
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // Strided axis pass (3D axis 1), one component per workgroup, tile of P columns.
 // ------------------------------------------------------------------------------------------
-// b: the workgroup's linear id over the (tile, outer, component) grid gx x gy x gz of one plan.
+// b: the workgroup's linear id over the (tile, outer, component) grid of one plan, after that of the
+// pending loop reductions.
 template <typename T, int L1, int L2, bool INV>
-__device__ __forceinline__ void axis_body(const AxisArgs<T>& a, int B, long long b, int gx, int gy, int gz)
+__device__ __forceinline__ void axis_body(const AxisArgs<T>& a, int B, int b)
 {
-    if (a.red_sc && b == 0) {
-        __shared__ double red[kThreads / 64];
-        finish_deferred(a.red_sc, a.partials, red);
-    }
+    if (a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
+    const int gx = a.ntiles, gy = a.outer;
     constexpr int L = L1 * L2;
     extern __shared__ __align__(16) unsigned char smem[];
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* Y = tw + L;
     const int P = a.P;
-    const long long lin = xcd_tile(b, (long long)gx * gy * gz);
+    TwiddleCopy<T, L> tc;
+    tc.load(a.twg);
+    const unsigned lin = (unsigned)xcd_tile(b, gx * gy * a.comps);
     const int tile = (int)(lin % gx);
     const int o = (int)((lin / gx) % gy);
-    const int c = (int)(lin / ((long long)gx * gy));
-    for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
-    lds_barrier();
+    const int c = (int)(lin / gx / gy);
     const cpx<T>* in = a.in + c * a.in_cs + o * a.in_os;
     cpx<T>* out = a.out + c * a.out_cs + o * a.out_os;
     // a band as long as the axis (GaNi) maps every position to itself: no band test then
     const bool banded = B != L;
-    for (int job = threadIdx.x; job < P * L1; job += blockDim.x) {
-        const int n1 = job / P;
-        const int p = job - n1 * P;
-        const int j = tile * P + p;
+    {
+        // step A
         cpx<T> s[L2];
+        int n1 = 0, p = 0;
+        auto load = [&](int job) {
+            n1 = job / P;
+            p = job - n1 * P;
+            const int j = tile * P + p;
 #pragma unroll
-        for (int n2 = 0; n2 < L2; n2++) {
-            const int pos = n1 + L1 * n2;
-            int si = pos;
-            bool ok = j < a.inner;
-            if (a.bin && banded) ok = ok && band_index(pos, L, B, &si);
-            s[n2] = ok ? in[(unsigned)(si * a.inner + j)] : cpx<T>{T(0), T(0)};
-        }
-        reg_dft<T, L2, INV>(s);
-        cpx<T>* y = Y + p * L + n1 * L2;
-        int m = 0;
+            for (int n2 = 0; n2 < L2; n2++) {
+                const int pos = n1 + L1 * n2;
+                int si = pos;
+                bool ok = j < a.inner;
+                if (a.bin && banded) ok = ok && band_index(pos, L, B, &si);
+                s[n2] = ok ? in[(unsigned)(si * a.inner + j)] : cpx<T>{T(0), T(0)};
+            }
+            reg_dft<T, L2, INV>(s);
+        };
+        auto write = [&]() {
+            cpx<T>* y = Y + p * L + n1 * L2;
+            int m = 0;
 #pragma unroll
-        for (int k2 = 0; k2 < L2; k2++) {
-            y[k2] = k2 ? cmul(s[k2], INV ? conj(tw[m]) : tw[m]) : s[k2];
-            m += n1;
-            if (m >= L) m -= L;
-        }
+            for (int k2 = 0; k2 < L2; k2++) {
+                y[k2] = k2 ? cmul(s[k2], INV ? conj(tw[m]) : tw[m]) : s[k2];
+                m += n1;
+                if (m >= L) m -= L;
+            }
+        };
+        run_jobs(P * L1, [&]() { tc.store(tw); }, load, write);
     }
     lds_barrier();
     for (int job = threadIdx.x; job < P * L2; job += blockDim.x) {
@@ -786,18 +956,14 @@ __device__ __forceinline__ void axis_body(const AxisArgs<T>& a, int B, long long
 template <typename T, int L1, int L2, bool INV>
 __global__ __launch_bounds__(kThreads) void k2_axis(AxisArgs<T> a, int B)
 {
-    axis_body<T, L1, L2, INV>(a, B, blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * blockIdx.z),
-                              gridDim.x, gridDim.y, gridDim.z);
+    axis_body<T, L1, L2, INV>(a, B, blockIdx.x);
 }
 
-// Several plans of one shape: grid (tiles, outer, d x members), member blockIdx.z / d.
+// Several plans of one shape: member blockIdx.y.
 template <typename T, int L1, int L2, bool INV>
-__global__ __launch_bounds__(kThreads) void k2_axis_b(const AxisArgs<T>* __restrict__ tab, int B, int d)
+__global__ __launch_bounds__(kThreads) void k2_axis_b(const AxisArgs<T>* __restrict__ tab, int B)
 {
-    const int m = (int)blockIdx.z / d;
-    const int cz = (int)blockIdx.z - m * d;
-    axis_body<T, L1, L2, INV>(tab[m], B, blockIdx.x + (long long)gridDim.x * (blockIdx.y + (long long)gridDim.y * cz),
-                              gridDim.x, gridDim.y, d);
+    axis_body<T, L1, L2, INV>(tab[blockIdx.y], B, blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -805,8 +971,9 @@ __global__ __launch_bounds__(kThreads) void k2_axis_b(const AxisArgs<T>* __restr
 // multiplier and inverse step B in registers -> LDS -> inverse step A.
 // ------------------------------------------------------------------------------------------
 template <typename T, int D, int L1, int L2, int MULT>
-__device__ __forceinline__ void middle_body(const MidArgs<T>& a, long long b, long long nb)
+__device__ __forceinline__ void middle_body(const MidArgs<T>& a, int b)
 {
+    if (D == 2 && a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     constexpr int L = L1 * L2;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -815,7 +982,7 @@ __device__ __forceinline__ void middle_body(const MidArgs<T>& a, long long b, lo
     const int P = a.P;
     const int YS = a.ys;      // LDS stride of a column (L, or L + 1 to spread the banks)
     const int PL = P * YS;
-    const int tile = (int)xcd_tile(b, nb);
+    const int tile = (int)xcd_tile(b, a.ntiles);
     for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
     lds_barrier();
     // forward step A: jobs (c, n1, p), p fastest
@@ -971,13 +1138,13 @@ __device__ __forceinline__ void middle_body(const MidArgs<T>& a, long long b, lo
 template <typename T, int D, int L1, int L2, int MULT>
 __global__ __launch_bounds__(kThreads) void k2_middle(MidArgs<T> a)
 {
-    middle_body<T, D, L1, L2, MULT>(a, blockIdx.x, gridDim.x);
+    middle_body<T, D, L1, L2, MULT>(a, blockIdx.x);
 }
 
 template <typename T, int D, int L1, int L2, int MULT>
 __global__ __launch_bounds__(kThreads) void k2_middle_b(const MidArgs<T>* __restrict__ tab)
 {
-    middle_body<T, D, L1, L2, MULT>(tab[blockIdx.y], blockIdx.x, gridDim.x);
+    middle_body<T, D, L1, L2, MULT>(tab[blockIdx.y], blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1062,10 +1229,14 @@ __device__ __forceinline__ double last_epilogue_tile(const LastArgs<T>& a, const
     const long long pt0 = row0 * L;
     const long long left = a.g.rows * (long long)L - pt0;
     const int lim = left < total ? (int)left : total;
-    // the Chebyshev and Eyre-Milton epilogues hold three more vectors per point: smaller chunks
-    constexpr int KU = (epi == EPI_CHEB || epi == EPI_EM) && ku_for(L) > KUH ? KUH : ku_for(L);
-    for (int base = 0; base < total; base += KU * blockDim.x)
-        acc += last_epilogue_chunk<T, D, L, epi, KU>(a, tab, base, total, lim, pt0, Zr, RowLen<L>{}, L + 1);
+    // the Chebyshev, Eyre-Milton and CGRX epilogues hold two or three more vectors per point: smaller chunks
+    constexpr int KU = (epi == EPI_CHEB || epi == EPI_EM || epi == EPI_CGRX) && ku_for(L) > KUH ? KUH : ku_for(L);
+    for (int base = 0; base < total; base += KU * blockDim.x) {
+        if (epi == EPI_CGR || epi == EPI_CGRX)  // point by point: the two have different chunks
+            acc = last_epilogue_chunk<T, D, L, epi, KU>(a, tab, base, total, lim, pt0, Zr, RowLen<L>{}, L + 1, acc);
+        else
+            acc += last_epilogue_chunk<T, D, L, epi, KU>(a, tab, base, total, lim, pt0, Zr, RowLen<L>{}, L + 1);
+    }
     return acc;
 }
 
@@ -1081,7 +1252,12 @@ __device__ __forceinline__ void last_body(const LastArgs<T>& a, int b, int nb)
     const T* Zr = reinterpret_cast<const T*>(Sx);
     T* tab = reinterpret_cast<T*>(Sx + npairs * (L + 1));
     __shared__ double red[kThreads / 64];
-    for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
+    // the twiddles share the spectra's memory latency in single precision (243^3: 81 -> 77 us); in
+    // double the registers they wait in cost more (125^3: 26.4 -> 27.8 us)
+    constexpr bool late = sizeof(T) == 4;
+    TwiddleCopy<T, L> tc;
+    tc.load(a.twg);
+    if (!late) tc.store(tw);
     if (epi == EPI_EM && a.A.kind == AK_PHASE)
         for (int m = threadIdx.x; m < kMaxPhases * 6; m += blockDim.x) tab[m] = T(a.A.tab_inv[m / 6][m % 6]);
     const long long row0 = xcd_tile(b, nb) * a.rpb;
@@ -1117,13 +1293,14 @@ __device__ __forceinline__ void last_body(const LastArgs<T>& a, int b, int nb)
                 }
             }
     }
+    if (late) tc.store(tw);
     lds_barrier();
     last_transform<T, D, L1, L2>(a, tw, Sx);
     const double acc = last_epilogue_tile<T, D, L, epi>(a, tab, row0, Zr);
     const double tot = block_sum(acc, red);
     if (threadIdx.x == 0) a.partials[b] = tot;
     if (a.defer_sc && b == 0 && threadIdx.x == 0) {
-        a.defer_sc->pend_n = nb;
+        a.defer_sc->pend = 1;
         a.defer_sc->pend_op = a.redop;
     }
 }
@@ -1349,7 +1526,7 @@ __device__ __forceinline__ void lastfirst_body(const LastArgs<T>& a, int b, int 
     const double tot = block_sum(acc, red);
     if (threadIdx.x == 0) a.partials[b] = tot;
     if (a.defer_sc && b == 0 && threadIdx.x == 0) {
-        a.defer_sc->pend_n = nb;
+        a.defer_sc->pend = 1;
         a.defer_sc->pend_op = a.redop;
     }
 }
