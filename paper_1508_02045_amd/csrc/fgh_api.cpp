@@ -147,6 +147,17 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
             break;
         }
     }
+    // mixed-radix rows: fewer rows per block where the launch would leave compute units idle (729^2
+    // FP32: 122 -> 365 blocks).  Rows pair into complex rows as before: in 2D a row's own two
+    // components do, in 3D even counts stay even.
+    if (!c.v2_row) {
+        const int step = d == 2 ? 1 : 2;
+        while (c.rpb > step && c.rpb % step == 0 && (g.rows + c.rpb - 1) / c.rpb < 256) c.rpb -= step;
+        const int npen = (c.rpb * d + 1) / 2;
+        c.lds_first = (size_t)(Ll + 2 * npen * Ll) * cs + tabb;
+        c.lds_first_v2 = (size_t)(Ll + npen * Ll) * cs + tabb;
+        c.lds_last_v2 = (size_t)(Ll + npen * (Ll + 1)) * cs + tabb;
+    }
     c.npen = (c.rpb * d + 1) / 2;
     const int Ps[5] = {16, 8, 4, 2, 1};
     c.P_axis = 1;
@@ -170,7 +181,10 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
         if (exact) P = pmid_cap;
         if (P > pmid_cap) continue;
         const size_t lds = c.v2_mid ? (size_t)(g.L[0] + d * P * g.L[0]) * cs : (size_t)(g.L[0] + (d + 1) * P * g.L[0]) * cs;
-        if (lds <= kLdsBudget || P == 1) {
+        // mixed-radix in 2D, where one half-spectrum row is all the columns there are: tiles narrow
+        // enough for one per compute unit (a column's arithmetic does not depend on the width)
+        const bool narrow = c.v2_mid || d == 3 || exact || (g.cols_mid + P - 1) / P >= 256;
+        if ((lds <= kLdsBudget && narrow) || P == 1) {
             c.P_mid = P;
             c.lds_mid = lds;
             break;
@@ -183,10 +197,10 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
 // index with 32 bits too, and a dense step is limited by the registers of a workgroup.  Lengths
 // whose smallest mixed-radix tile exceeds the LDS stay refused.
 //
-// They serve every double-precision application and fgh_apply_f32.  The single-precision loops of
-// refined solves keep the mixed-radix passes: the rounding of an inner solve enters a refined
-// result at about 1e-8 of it (the outer loop stops at the caller's tolerance), and those results
-// stay what they have been.
+// They serve fgh_apply, fgh_apply_f32 and double-precision solves.  Refined solves keep the
+// mixed-radix passes in both precisions: the rounding of an inner solve enters a refined result at
+// about 1e-8 of it (the outer loop stops at the caller's tolerance), where the residual is rounded
+// to single precision too, and those results stay what they have been.
 void use_run_time_lengths(const Geo& g, size_t cs, size_t rs, Config* c)
 {
     const int d = g.d;
@@ -363,7 +377,8 @@ struct fgh_plan_s {
     int nphase;
     double tab[kMaxPhases][6];
     int ncoef_op;             // 1 (scalar A_{2N-1} / iso) or ncoef
-    OpPlan op64, op32;
+    OpPlan op64, op32;        // the solves' operators
+    OpPlan ap64, ap32;        // the applications' (run-time lengths also on refined plans)
     double* r64;
     double* p64;
     double* q64;
@@ -2269,7 +2284,7 @@ fgh_status fgh_plan_create(fgh_plan* out, int d, const int32_t* N, fgh_rule rule
             for (int q = 0; q < nc; q++)
                 if (!std::isfinite(p->tab[i][q])) return fail(FGH_E_NOT_SPD);
     fill_opplan(p, &p->op64, false);
-    set_run_time_lengths(&p->op64, false);
+    if (precision == FGH_FP64) set_run_time_lengths(&p->op64, false);
     fill_opplan(p, &p->op32, true);
     const long long nv = (long long)d * p->g.npts;
     double* v64 = reinterpret_cast<double*>(p->ws + p->lay.vec64);
@@ -2435,6 +2450,12 @@ fgh_status fgh_plan_create(fgh_plan* out, int d, const int32_t* N, fgh_rule rule
     if (precision == FGH_FP32_REFINED && (s = tune_fused(p, &p->op32, true, p->r32))) return fail(s);
     if ((s = tune_first_cg(p, &p->op64, false))) return fail(s);
     if (precision == FGH_FP32_REFINED && (s = tune_first_cg(p, &p->op32, true))) return fail(s);
+    p->ap64 = p->op64;
+    p->ap32 = p->op32;
+    if (precision == FGH_FP32_REFINED) {
+        set_run_time_lengths(&p->ap64, false);
+        set_run_time_lengths(&p->ap32, true);
+    }
     if (hipStreamSynchronize(p->stream) != hipSuccess) return fail(FGH_E_DEVICE);
     *out = p;
     return FGH_OK;
@@ -2499,6 +2520,18 @@ fgh_status fgh_plan_bounds(fgh_plan p, double* c_A, double* C_A)
     return FGH_OK;
 }
 
+// The operator of a plain application: the passes chosen at plan creation with the plan's current
+// stream, coefficients and profiler.
+static OpPlan apply_plan(fgh_plan p, bool f32)
+{
+    const OpPlan& s = f32 ? p->op32 : p->op64;
+    OpPlan op = f32 ? p->ap32 : p->ap64;
+    op.stream = s.stream;
+    op.A = s.A;
+    op.prof = s.prof;
+    return op;
+}
+
 fgh_status fgh_apply(fgh_plan p, const double* x, double* y)
 {
     if (!p || !x || !y) return FGH_E_INVALID;
@@ -2509,7 +2542,7 @@ fgh_status fgh_apply(fgh_plan p, const double* x, double* y)
     a.sgn = 1.0;
     a.y = y;
     int nb = 0;
-    HIPOK(run_apply<double>(p->op64, a, &nb));
+    HIPOK(run_apply<double>(apply_plan(p, false), a, &nb));
     return FGH_OK;
 }
 
@@ -2523,10 +2556,8 @@ fgh_status fgh_apply_f32(fgh_plan p, const float* x, float* y)
     a.epi = EPI_STORE;
     a.sgn = 1.0;
     a.y = y;
-    OpPlan op = p->op32;
-    set_run_time_lengths(&op, true);
     int nb = 0;
-    HIPOK(run_apply<float>(op, a, &nb));
+    HIPOK(run_apply<float>(apply_plan(p, true), a, &nb));
     return FGH_OK;
 }
 

@@ -117,3 +117,29 @@ def test_solvers_any_length(N, solver):
     diff = np.linalg.norm(e.cpu().numpy() - ref.e) / np.linalg.norm(ref.e + E.reshape((d,) + (1,) * d))
     plan.close()
     assert diff <= 1e-9
+
+
+@pytest.mark.parametrize("N,rule", [((85, 33), 0), ((81, 169), 0), ((35, 105), 0), ((61, 13), 0), ((2187, 3), 0), ((2401, 3), 0),
+                                    ((27, 11), 1), ((21, 15, 27), 0), ((17, 49, 11), 0),
+                                    ((9, 75, 25), 0), ((11, 9, 13), 1)])
+@pytest.mark.parametrize("solver", ["cg", "eyre_milton", "chebyshev"])
+def test_refined_solves_any_length(N, rule, solver):
+    """Refined solves (mixed-radix passes: paired radices, direct sums spread over a workgroup, all
+    components in one transform or one after the other) against the FP64 solve of the same problem
+    (run-time-length passes).  Both stop on a residual (step) of 1e-9 relative; the solutions then
+    differ by at most that times the condition number 10, with a factor 10 in hand: 1e-7."""
+    if solver == "eyre_milton" and rule == 1:
+        pytest.skip("Eyre-Milton has no exact-integration form")
+    d = len(N)
+    phase = torch.from_numpy(inputs.paper_square(N)).cuda()
+    tab = inputs.sym_pack(inputs.iso_tables(d, [1.0, 10.0])).T
+    E = np.eye(d)[d - 1]
+    e = []
+    for prec in (fgh.FGH_FP64, fgh.FGH_FP32_REFINED):
+        plan = fgh.Plan(N, rule=rule, precision=prec, phase=phase, phase_table=tab)
+        x, st, stats = plan.solve(solver, E, 1e-9)
+        assert st == fgh.FGH_OK
+        e.append(x.cpu().numpy())
+        plan.close()
+    full = np.linalg.norm(e[0] + E.reshape((d,) + (1,) * d))
+    assert np.linalg.norm(e[0] - e[1]) <= 1e-7 * full
