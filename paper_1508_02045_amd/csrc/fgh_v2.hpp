@@ -856,22 +856,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     first_body<T, D, L1, L2>(tab[blockIdx.y], op, blockIdx.x, gridDim.x);
 }
 
-// Step-A jobs of a strided or middle pass: load a subsequence and transform it, then write it to LDS
-// times its twiddles; table() puts those there.  A thread's first job runs up to its twiddles ahead
-// of the table's barrier, so that the pass starts with one memory latency instead of two (243^3:
-// strided passes 173 and 157 -> 158 and 140 us).  The loads stay in one block with the transform:
-// apart from it the compiler contracts other products, and refined solves keep their rounding.
-template <typename FT, typename FL, typename FX>
+// Step-A jobs of the strided pass: load a subsequence and transform it, then write it to LDS times its
+// twiddles; table() puts those there.  EARLY: a thread's first job runs up to its twiddles ahead of
+// the table's barrier, so that the pass starts with one memory latency instead of two.  That pays
+// for the long subsequences (243^3 FP64: 173 and 157 -> 158 and 140 us, 125^3 FP32: 15.1 -> 12.4 us);
+// at 135^3 FP64 the registers held across the barrier cost more (22.6 -> 23.6 us).  The loads stay
+// in one block with the transform: apart from it the compiler contracts other products, and refined
+// solves keep their rounding.
+template <bool EARLY, typename FT, typename FL, typename FX>
 __device__ __forceinline__ void run_jobs(int n, FT table, FL load_transform, FX write)
 {
     int job = threadIdx.x;
-    if (job < n) load_transform(job);
+    if (EARLY && job < n) load_transform(job);
     table();
     lds_barrier();
-    while (job < n) {
-        write();
-        job += blockDim.x;
-        if (job < n) load_transform(job);
+    if (EARLY) {
+        while (job < n) {
+            write();
+            job += blockDim.x;
+            if (job < n) load_transform(job);
+        }
+    } else {
+        for (; job < n; job += blockDim.x) {
+            load_transform(job);
+            write();
+        }
     }
 }
 
@@ -929,7 +938,7 @@ __device__ __forceinline__ void axis_body(const AxisArgs<T>& a, int B, int b)
                 if (m >= L) m -= L;
             }
         };
-        run_jobs(P * L1, [&]() { tc.store(tw); }, load, write);
+        run_jobs<(L2 >= 25)>(P * L1, [&]() { tc.store(tw); }, load, write);
     }
     lds_barrier();
     for (int job = threadIdx.x; job < P * L2; job += blockDim.x) {
