@@ -940,15 +940,17 @@ fgh_status rhs(fgh_plan p, const double* E, T* r, double* bb, double* ae2)
     a.y = r;
     int nb = 0;
     HIPOK(run_apply<T>(op, a, &nb));
-    fgh_status st = reduce_read(p, op, nb, RED_SET_RR, bb);
-    if (st) return st;
+    HIPOK(run_reduce_async(op, nb, RED_SET_RR));
     if (ae2) {
         HIPOK(run_norm_AE(p->op64, E, &nb));
-        double v;
-        st = reduce_read(p, p->op64, nb, RED_TOTAL, &v);
-        if (st) return st;
-        *ae2 = v;
+        HIPOK(run_reduce_async(p->op64, nb, RED_TOTAL));
     }
+    // one readback for both sums: rr is the first reduction's, total the last one's
+    const Scalars* h = reinterpret_cast<const Scalars*>(p->host_buf);
+    HIPOK(hipMemcpyAsync(p->host_buf, op.sc, sizeof(Scalars), hipMemcpyDeviceToHost, p->stream));
+    HIPOK(hipStreamSynchronize(p->stream));
+    *bb = h->rr;
+    if (ae2) *ae2 = h->total;
     return FGH_OK;
 }
 
@@ -996,6 +998,35 @@ void drop_graph(fgh_plan p)
     p->gkey = 0;
 }
 
+// How many graphs of bodies to enqueue before the next look at the loop's scalars: enough for the
+// bodies that remain at the rate since the last look (in the logarithm of the test quantity; to the
+// body limit where there is no test), at most kMaxChunk.  Bodies after the stop return at once, but
+// each still costs its launches: a 56-body loop ended 32 bodies late with chunks that only doubled.
+constexpr int kMaxChunk = 4;
+struct ChunkPlan {
+    int m = 0, chunk = 1;
+    double last;  // the test quantity at m (its scale before the first body)
+    explicit ChunkPlan(double scale) : last(scale) {}
+    int next(const Scalars* h)
+    {
+        double need = -1.0;
+        if (h->thr < 0.0) {
+            need = h->limit - h->m;
+        } else if (h->m > m && h->last > 0.0 && h->last < last && h->thr > 0.0) {
+            need = std::log(h->last / h->thr) * (h->m - m) / std::log(last / h->last);
+        }
+        if (need >= 0.0) {
+            const double graphs = std::ceil((need + 1.0) / kGraphBodies);  // the end is seen a body late
+            chunk = graphs < 1.0 ? 1 : graphs > kMaxChunk ? kMaxChunk : (int)graphs;
+        } else {
+            chunk = std::min(2 * chunk, kMaxChunk);
+        }
+        m = h->m;
+        last = h->last;
+        return chunk;
+    }
+};
+
 // Run loop bodies in chunks; the device decides when to stop (Scalars::done) and counts the
 // bodies, so the host synchronises once per chunk instead of once per body.  When the plan's
 // stream can be captured, kGraphBodies bodies are captured once into a HIP graph (keyed by the
@@ -1032,8 +1063,8 @@ fgh_status run_loop(fgh_plan p, const OpPlan& op, Body body, uint64_t key, bool 
         HIPOK(hipGraphInstantiate(&p->gexec, g, nullptr, nullptr, 0));
         p->gkey = key;
     }
-    int chunk = 1;
-    for (;;) {
+    ChunkPlan plan(scale);
+    for (int chunk = 1;; chunk = plan.next(h)) {
         for (int k = 0; k < chunk; k++) {
             if (use_graph) {
                 HIPOK(hipGraphLaunch(p->gexec, op.stream));
@@ -1044,7 +1075,6 @@ fgh_status run_loop(fgh_plan p, const OpPlan& op, Body body, uint64_t key, bool 
         HIPOK(hipMemcpyAsync(p->host_buf, op.sc, sizeof(Scalars), hipMemcpyDeviceToHost, op.stream));
         HIPOK(hipStreamSynchronize(op.stream));
         if (h->done) break;
-        if (chunk < 4) chunk *= 2;
     }
     out->iters = h->m;
     out->res = scale > 0 ? h->last / scale : h->last;
@@ -1149,16 +1179,17 @@ hipError_t cg_body(const OpPlan& op, const CgPlan& c, long long n, T* x, T* r, T
 }
 
 // Conjugate gradients (Algorithm 2) for C x = b with b already in r, x = 0 on entry.  Stops when
-// ||r_m|| <= tol_rel ||b|| (recursive residual) or after `fixed` bodies.
+// ||r_m|| <= tol_rel ||b|| (recursive residual) or after `fixed` bodies.  bb: (b, b) where it is
+// known (< 0: summed here).
 template <typename T>
-fgh_status cg_core(fgh_plan p, T* x, T* r, T* pv, T* q, double tol_rel, int max_iter, int fixed, SolveOut* out)
+fgh_status cg_core(fgh_plan p, T* x, T* r, T* pv, T* q, double tol_rel, int max_iter, int fixed, SolveOut* out,
+                   double bb = -1.0)
 {
     const OpPlan& op = opp<T>(p);
     const long long n = (long long)p->d * p->g.npts;
     const double S = (double)p->g.npts;
     HIPOK(run_copy<T>(p->stream, n, pv, r));
-    double bb = 0.0;
-    {
+    if (bb < 0.0) {
         int nb = 0;
         HIPOK(run_dot<T>(op, n, r, r, &nb));
         fgh_status st0 = reduce_read(p, op, nb, RED_TOTAL, &bb);
@@ -1209,14 +1240,13 @@ hipError_t fused_prologue(const OpPlan& op, ApplyArgs a)
 // that is Richardson's iteration x += (1/delta)(b - C x) on an explicit right-hand side.
 template <typename T>
 fgh_status cheb_core(fgh_plan p, T* x, T* r, T* pv, double tol_rel, int max_iter, int fixed, SolveOut* out,
-                     double c_in = -1.0, double delta_in = 0.0)
+                     double c_in = -1.0, double delta_in = 0.0, double bb = -1.0)
 {
     const OpPlan& op = opp<T>(p);
     const long long n = (long long)p->d * p->g.npts;
     const double S = (double)p->g.npts;
     HIPOK(run_copy<T>(p->stream, n, pv, r));
-    double bb = 0.0;
-    {
+    if (bb < 0.0) {
         int nb = 0;
         HIPOK(run_dot<T>(op, n, r, r, &nb));
         fgh_status st0 = reduce_read(p, op, nb, RED_TOTAL, &bb);
@@ -1414,8 +1444,9 @@ fgh_status hist_arm(fgh_plan p, const double* E, int j, const double* x, bool wh
     return FGH_OK;
 }
 
+// *bbo: (b, b) where the solver formed the right-hand side (left as it is otherwise).
 fgh_status solve_one_fp64(fgh_plan p, int solver, const double* E, double tol, int max_iter, int fixed, double* e,
-                          fgh_stats* st, int load)
+                          fgh_stats* st, int load, double* bbo)
 {
     struct Disarm {
         fgh_plan p;
@@ -1431,6 +1462,7 @@ fgh_status solve_one_fp64(fgh_plan p, int solver, const double* E, double tol, i
     fgh_status s;
     if (solver == FGH_CG || solver == FGH_CHEBYSHEV) {
         if ((s = rhs<double>(p, E, p->r64, &bb, &ae2))) return s;
+        *bbo = bb;
         HIPOK(run_fill<double>(p->stream, n, e, 0.0));
         const bool zero = !(std::sqrt(bb / S) > kZeroRhs * std::sqrt(ae2 / S));
         if ((s = hist_arm(p, E, load, e, false))) return s;
@@ -1444,9 +1476,9 @@ fgh_status solve_one_fp64(fgh_plan p, int solver, const double* E, double tol, i
                 HIPOK(p->hist_fn());
             }
         } else if (solver == FGH_CG) {
-            if ((s = cg_core<double>(p, e, p->r64, p->p64, p->q64, tol, max_iter, fixed, &so))) return s;
+            if ((s = cg_core<double>(p, e, p->r64, p->p64, p->q64, tol, max_iter, fixed, &so, bb))) return s;
         } else {
-            if ((s = cheb_core<double>(p, e, p->r64, p->p64, tol, max_iter, fixed, &so))) return s;
+            if ((s = cheb_core<double>(p, e, p->r64, p->p64, tol, max_iter, fixed, &so, -1.0, 0.0, bb))) return s;
         }
     } else if (solver == FGH_RICHARDSON) {
         HIPOK(run_fill<double>(p->stream, n, e, 0.0));
@@ -1484,7 +1516,7 @@ fgh_status solve_one_fp64(fgh_plan p, int solver, const double* E, double tol, i
 //    iterated in FP32 from delta = 0; x += delta; stop when ||dbar|| <= tol |E| (then x takes
 //    that last FP64 step, as Algorithm 4 would).
 fgh_status solve_one_refined(fgh_plan p, int solver, const double* E, double tol, int max_iter, double* e,
-                             fgh_stats* st)
+                             fgh_stats* st, double* bbo)
 {
     const long long n = (long long)p->d * p->g.npts;
     const double S = (double)p->g.npts;
@@ -1550,6 +1582,7 @@ fgh_status solve_one_refined(fgh_plan p, int solver, const double* E, double tol
         HIPOK(run_fill<double>(p->stream, n, e, 0.0));
         double bb = 0.0, ae2 = 0.0;
         if ((s = rhs<double>(p, E, p->r64, &bb, &ae2))) return s;
+        *bbo = bb;
         applies64++;
         const bool zero = !(std::sqrt(bb / S) > kZeroRhs * std::sqrt(ae2 / S));
         const double normb = std::sqrt(bb / S);
@@ -1618,6 +1651,7 @@ fgh_status solve_one_refined(fgh_plan p, int solver, const double* E, double tol
         HIPOK(run_fill<double>(p->stream, n, e, 0.0));
         double bb = 0.0;
         if ((s = rhs<double>(p, E, p->r64, &bb, nullptr))) return s;
+        *bbo = bb;
         applies64++;
         double rr = bb;
         bool done = false;
@@ -1828,8 +1862,9 @@ fgh_status run_loop_batch(fgh_plan lead, const std::vector<BatchMember*>& A, hip
         lead->gkey = key;
     }
     const int nb = (int)A.size();
-    int chunk = 1;
-    for (;;) {
+    std::vector<ChunkPlan> plans;
+    for (int k = 0; k < nb; k++) plans.emplace_back(scale[k]);
+    for (int chunk = 1;;) {
         for (int k = 0; k < chunk; k++) {
             if (use_graph) {
                 HIPOK(hipGraphLaunch(lead->gexec, s));
@@ -1841,9 +1876,14 @@ fgh_status run_loop_batch(fgh_plan lead, const std::vector<BatchMember*>& A, hip
             HIPOK(hipMemcpyAsync(A[k]->p->host_buf, A[k]->p->op32.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
         HIPOK(hipStreamSynchronize(s));
         bool all = true;
-        for (int k = 0; k < nb; k++) all = all && reinterpret_cast<const Scalars*>(A[k]->p->host_buf)->done != 0;
+        chunk = 1;
+        for (int k = 0; k < nb; k++) {
+            const Scalars* h = reinterpret_cast<const Scalars*>(A[k]->p->host_buf);
+            if (h->done) continue;
+            all = false;
+            chunk = std::max(chunk, plans[k].next(h));
+        }
         if (all) break;
-        if (chunk < 4) chunk *= 2;
     }
     outs->assign(nb, SolveOut{});
     for (int k = 0; k < nb; k++) {
@@ -2657,11 +2697,12 @@ static fgh_status solve_common(fgh_plan p, fgh_solver solver, const double* E, i
         double* ej = e + j * n;
         fgh_stats st{};
         const auto t0 = std::chrono::steady_clock::now();
+        double bb = -1.0;  // (b, b), where the solve has formed it
         fgh_status s;
         if (p->prec == FGH_FP32_REFINED && fixed <= 0)
-            s = solve_one_refined(p, solver, Ej, tol, max_iter, ej, &st);
+            s = solve_one_refined(p, solver, Ej, tol, max_iter, ej, &st, &bb);
         else
-            s = solve_one_fp64(p, solver, Ej, tol, max_iter, fixed, ej, &st, j);
+            s = solve_one_fp64(p, solver, Ej, tol, max_iter, fixed, ej, &st, j, &bb);
         if (s) return s;
         if (hipStreamSynchronize(p->stream) != hipSuccess) return FGH_E_DEVICE;
         const auto t1 = std::chrono::steady_clock::now();
@@ -2669,8 +2710,7 @@ static fgh_status solve_common(fgh_plan p, fgh_solver solver, const double* E, i
         st.c_A = p->cA;
         st.C_A = p->CA;
         // true residual at exit (not timed)
-        double bb = 0.0;
-        if ((s = rhs<double>(p, Ej, p->r64, &bb, nullptr))) return s;
+        if (bb < 0.0 && (s = rhs<double>(p, Ej, p->r64, &bb, nullptr))) return s;
         double rt = 0.0;
         if ((s = true_residual(p, Ej, ej, bb, &rt))) return s;
         st.rel_res_true = rt;
