@@ -87,6 +87,14 @@ bool factorize(int L, Axis* ax)
     return true;
 }
 
+// No prime factor above 7: the mixed-radix passes have a butterfly for every radix.
+bool small_radices(int L)
+{
+    for (int p : {3, 5, 7})
+        while (L % p == 0) L /= p;
+    return L == 1;
+}
+
 struct Config {
     int rpb, npen, P_axis, P_mid;
     size_t lds_first, lds_first_v2, lds_last_v2, lds_axis, lds_mid;
@@ -148,9 +156,10 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
         }
     }
     // mixed-radix rows: fewer rows per block where the launch would leave compute units idle (729^2
-    // FP32: 122 -> 365 blocks).  Rows pair into complex rows as before: in 2D a row's own two
-    // components do, in 3D even counts stay even.
-    if (!c.v2_row) {
+    // FP32: 122 -> 365 blocks, last pass 35 -> 20 us).  Rows pair into complex rows as before: in 2D a
+    // row's own two components do, in 3D even counts stay even.  Not with direct sums, whose few
+    // threads per row want the rows of a block side by side (101 x 67: 170 -> 176 ms per solve).
+    if (!c.v2_row && small_radices(Ll)) {
         const int step = d == 2 ? 1 : 2;
         while (c.rpb > step && c.rpb % step == 0 && (g.rows + c.rpb - 1) / c.rpb < 256) c.rpb -= step;
         const int npen = (c.rpb * d + 1) / 2;
@@ -182,8 +191,9 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
         if (P > pmid_cap) continue;
         const size_t lds = c.v2_mid ? (size_t)(g.L[0] + d * P * g.L[0]) * cs : (size_t)(g.L[0] + (d + 1) * P * g.L[0]) * cs;
         // mixed-radix in 2D, where one half-spectrum row is all the columns there are: tiles narrow
-        // enough for one per compute unit (a column's arithmetic does not depend on the width)
-        const bool narrow = c.v2_mid || d == 3 || exact || (g.cols_mid + P - 1) / P >= 256;
+        // enough for one per compute unit (729^2 FP32: 60 -> 33 us; a column's arithmetic does not
+        // depend on the width), direct sums again excepted
+        const bool narrow = c.v2_mid || d == 3 || exact || !small_radices(g.L[0]) || (g.cols_mid + P - 1) / P >= 256;
         if ((lds <= kLdsBudget && narrow) || P == 1) {
             c.P_mid = P;
             c.lds_mid = lds;

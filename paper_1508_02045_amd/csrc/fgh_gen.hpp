@@ -393,6 +393,52 @@ __global__ __launch_bounds__(kGenMaxThreads) void kg_last(LastArgs<T> a)
     }
 }
 
+// The last pass of one loop body with the first pass of the next (Richardson, Chebyshev, Eyre-Milton),
+// as k2_lastfirst: a point's update and its next z = A u are one thread's, which writes z into the
+// slot its y came from; the rows are then transformed forward in place.
+template <typename T, int D, int epi, int NI>
+__global__ __launch_bounds__(kGenMaxThreads) void kg_lastfirst(LastArgs<T> a)
+{
+    if (a.done && *a.done) return;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[kGenMaxThreads / 64];
+    const int L = a.ax.L, npen = a.npen;
+    cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
+    cpx<T>* Z = tw + L;
+    T* tab = reinterpret_cast<T*>(Z + npen * L);
+    T* tabinv = tab + kMaxPhases * 6;
+    for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
+    if (a.A.kind == AK_PHASE)
+        for (int m = threadIdx.x; m < kMaxPhases * 6; m += blockDim.x) {
+            tab[m] = T(a.A.tab[m / 6][m % 6]);
+            tabinv[m] = T(a.A.tab_inv[m / 6][m % 6]);
+        }
+    const long long row0 = xcd_tile(blockIdx.x, gridDim.x) * a.rpb;
+    const int nrows = (int)(a.g.rows - row0 < a.rpb ? a.g.rows - row0 : a.rpb);
+    load_half_spectra<T, D>(a.g, L, a.in, row0, nrows, npen, Z);
+    lds_barrier();
+    row_transform<T, true, NI>(Z, a.ax, npen, tw);
+    const RowLen<0> rl{L, 1.0f / (float)L};
+    constexpr int KU = 2;
+    double acc = 0.0;
+    for (int base = 0; base < a.rpb * L; base += KU * blockDim.x)
+        acc += lastfirst_chunk<T, D, 0, epi, KU>(a, tab, tabinv, base, a.rpb * L, nrows * L, row0 * L,
+                                                 reinterpret_cast<T*>(Z), rl, L);
+    if ((a.rpb * D) & 1)  // the imaginary half of the last packed row is a zero row
+        for (int i = threadIdx.x; i < L; i += blockDim.x) Z[(npen - 1) * L + i].y = T(0);
+    lds_barrier();
+    row_transform<T, false, NI>(Z, a.ax, npen, tw);
+    store_half_spectra<T, D>(a.g, L, a.out, row0, nrows, Z);
+    const double tot = block_sum(acc, red);
+    if (threadIdx.x == 0) {
+        a.partials[blockIdx.x] = tot;
+        if (a.defer_sc && blockIdx.x == 0) {
+            a.defer_sc->pend = 1;
+            a.defer_sc->pend_op = a.redop;
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // Strided axis pass (3D axis 1), one component per workgroup, tile of P columns kept column
 // fastest.  NI = 0 loads the step-A subsequences from global memory straight into registers.

@@ -63,6 +63,35 @@ hipError_t gen_last(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned n
     return hipErrorInvalidValue;
 }
 
+template <typename T, int D, int EPI, int NI>
+static hipError_t gen_lastfirst_ni(const OpPlan& op, const LastArgs<T>& la, unsigned nblk)
+{
+    LAUNCH_LDS_T((kg_lastfirst<T, D, EPI, NI>), dim3(nblk), op.th_row, op.lds_fused, op.stream, la);
+    return hipGetLastError();
+}
+
+template <typename T, int EPI>
+static hipError_t gen_lastfirst_epi(const OpPlan& op, const LastArgs<T>& la, unsigned nblk)
+{
+#define C(N) (op.g.d == 2 ? gen_lastfirst_ni<T, 2, EPI, N>(op, la, nblk) : gen_lastfirst_ni<T, 3, EPI, N>(op, la, nblk))
+    FGH_GEN_NI(op.ni_row, C);
+#undef C
+}
+
+// Double precision only, as the loops.
+template <typename T>
+hipError_t gen_lastfirst(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned nblk)
+{
+    if constexpr (sizeof(T) == 8) {
+        switch (epi) {
+            case EPI_RICH: return gen_lastfirst_epi<T, EPI_RICH>(op, la, nblk);
+            case EPI_CHEB: return gen_lastfirst_epi<T, EPI_CHEB>(op, la, nblk);
+            case EPI_EM: return gen_lastfirst_epi<T, EPI_EM>(op, la, nblk);
+        }
+    }
+    return hipErrorInvalidValue;
+}
+
 template <typename T, int NI>
 static hipError_t gen_axis_ni(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int B)
 {
@@ -107,6 +136,7 @@ hipError_t gen_middle(const OpPlan& op, const MidArgs<T>& ma, int mult)
 #define FGH_GEN_INSTANTIATE(T)                                                             \
     template hipError_t gen_first<T>(const OpPlan&, const FirstArgs<T>&, int, unsigned);   \
     template hipError_t gen_last<T>(const OpPlan&, const LastArgs<T>&, int, unsigned);     \
+    template hipError_t gen_lastfirst<T>(const OpPlan&, const LastArgs<T>&, int, unsigned); \
     template hipError_t gen_axis<T>(const OpPlan&, const AxisArgs<T>&, bool, int);         \
     template hipError_t gen_middle<T>(const OpPlan&, const MidArgs<T>&, int);
 

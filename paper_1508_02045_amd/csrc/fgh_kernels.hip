@@ -1183,6 +1183,7 @@ static hipError_t v2_lastfirst_epi(const OpPlan& op, const LastArgs<T>& la, unsi
 template <typename T, int D>
 static hipError_t v2_lastfirst(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned* nblk)
 {
+    if (op.gen_row) return gen_lastfirst<T>(op, la, epi, *nblk);
     switch (epi) {
         case EPI_RICH: return v2_lastfirst_epi<T, D, EPI_RICH>(op, la, nblk);
         case EPI_CHEB: return v2_lastfirst_epi<T, D, EPI_CHEB>(op, la, nblk);

@@ -138,12 +138,14 @@ hipError_t gen_first(const OpPlan& op, const FirstArgs<T>& fa, int opc, unsigned
 template <typename T>
 hipError_t gen_last(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned nblk);
 template <typename T>
+hipError_t gen_lastfirst(const OpPlan& op, const LastArgs<T>& la, int epi, unsigned nblk);
+template <typename T>
 hipError_t gen_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int B);
 template <typename T>
 hipError_t gen_middle(const OpPlan& op, const MidArgs<T>& ma, int mult);
 
 // Whether the plan's last pass can run the next body's first pass (see ApplyArgs::next_op).
-inline bool fusable(const OpPlan& op) { return op.v2_row; }
+inline bool fusable(const OpPlan& op) { return op.v2_row || op.gen_row; }
 
 template <typename T>
 hipError_t run_apply(const OpPlan& op, const ApplyArgs& a, int* nblocks_last);

@@ -143,3 +143,26 @@ def test_refined_solves_any_length(N, rule, solver):
         plan.close()
     full = np.linalg.norm(e[0] + E.reshape((d,) + (1,) * d))
     assert np.linalg.norm(e[0] - e[1]) <= 1e-7 * full
+
+
+@pytest.mark.parametrize("N,rule", [((51, 85), 0), ((33, 97), 0), ((85, 85), 1), ((17, 15, 19), 0), ((37, 9, 21), 0),
+                                    ((9, 11, 13), 1)])
+@pytest.mark.parametrize("solver", ["richardson", "chebyshev", "eyre_milton"])
+def test_fused_bodies_any_length(N, rule, solver, monkeypatch):
+    """The last pass fused with the next body's first (run-time lengths) against the separate passes
+    (FGH_FUSE=0): the same operations on the same values, so a product contracted differently by
+    the compiler is all that may differ -- 7 bodies of a contraction, 1e-13 of the field."""
+    if solver == "eyre_milton" and rule == 1:
+        pytest.skip("Eyre-Milton has no exact-integration form")
+    d = len(N)
+    rng = np.random.default_rng(sum(N))
+    A = torch.from_numpy(1.0 + 9.0 * rng.random(N)).cuda()
+    plan = fgh.Plan(N, rule=rule, A=A)
+    e = []
+    for on in ("0", "1"):
+        monkeypatch.setenv("FGH_FUSE", on)
+        x, st, stats = plan.solve_fixed(solver, np.eye(d)[0], 7)
+        assert st == fgh.FGH_OK and stats[0]["iters"] == 7
+        e.append(x.cpu().numpy())
+    plan.close()
+    assert np.linalg.norm(e[0] - e[1]) <= 1e-13 * np.sqrt(e[0][0].size)
