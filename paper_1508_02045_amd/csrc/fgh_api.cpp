@@ -157,9 +157,9 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
     }
     // mixed-radix rows: fewer rows per block where the launch would leave compute units idle (729^2
     // FP32: 122 -> 365 blocks, last pass 35 -> 20 us).  Rows pair into complex rows as before: in 2D a
-    // row's own two components do, in 3D even counts stay even.  Not with direct sums, whose few
-    // threads per row want the rows of a block side by side (101 x 67: 170 -> 176 ms per solve).
-    if (!c.v2_row && small_radices(Ll)) {
+    // row's own two components do, in 3D even counts stay even (and, with direct sums, all: a thread
+    // per butterfly wants the rows of a block side by side).
+    if (!c.v2_row && (d == 2 || small_radices(Ll))) {
         const int step = d == 2 ? 1 : 2;
         while (c.rpb > step && c.rpb % step == 0 && (g.rows + c.rpb - 1) / c.rpb < 256) c.rpb -= step;
         const int npen = (c.rpb * d + 1) / 2;
@@ -192,8 +192,8 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
         const size_t lds = c.v2_mid ? (size_t)(g.L[0] + d * P * g.L[0]) * cs : (size_t)(g.L[0] + (d + 1) * P * g.L[0]) * cs;
         // mixed-radix in 2D, where one half-spectrum row is all the columns there are: tiles narrow
         // enough for one per compute unit (729^2 FP32: 60 -> 33 us; a column's arithmetic does not
-        // depend on the width), direct sums again excepted
-        const bool narrow = c.v2_mid || d == 3 || exact || !small_radices(g.L[0]) || (g.cols_mid + P - 1) / P >= 256;
+        // depend on the width)
+        const bool narrow = c.v2_mid || d == 3 || exact || (g.cols_mid + P - 1) / P >= 256;
         if ((lds <= kLdsBudget && narrow) || P == 1) {
             c.P_mid = P;
             c.lds_mid = lds;
@@ -283,14 +283,7 @@ Layout make_layout(const Geo& g, const int32_t* N, int rule, int prec, int akind
     if (v64 < (size_t)d * sp * 16) v64 = (size_t)d * sp * 16;
     l.vec64 = take(v64);
     l.vec32 = take(prec == FGH_FP32_REFINED ? (size_t)4 * nv * 4 : 0);
-    // partial sums: one per block of the last pass, whichever row kernels a precision may use
-    long long nb = 0;
-    for (int f32 = 0; f32 < 2; f32++) {
-        Config c = choose_config(g, f32 ? 8 : 16, f32 ? 4 : 8);
-        nb = std::max(nb, (g.rows + c.rpb - 1) / c.rpb);
-        use_run_time_lengths(g, f32 ? 8 : 16, f32 ? 4 : 8, &c);
-        if (c.row.ok) nb = std::max(nb, (g.rows + c.row.n - 1) / c.row.n);
-    }
+    const long long nb = g.rows;  // one partial sum per block of the last pass: at most one per row
     long long np = nb;
     if (np < 1024 * 2 + 2) np = 1024 * 2 + 2;
     if (np < 512 * 18) np = 512 * 18;

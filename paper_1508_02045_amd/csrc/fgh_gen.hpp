@@ -29,8 +29,6 @@ constexpr int kGenMaxItems = 4;     // products per wavefront
 
 #define FGH_GEN_RADICES(X) X(1) X(3) X(5) X(7) X(9) X(11) X(13) X(15) X(17)
 
-__device__ __forceinline__ int fdiv(int i, float inv) { return (int)(((float)i + 0.5f) * inv); }
-
 template <typename T>
 struct Mfma;
 template <>

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kThreads) void k_first(FirstArgs<T> a)
         if (threadIdx.x == 0) a.pq_part[blockIdx.x] = tot;
     }
     __syncthreads();
-    cpx<T>* res = fft_lds<T, false>(b0, b1, a.ax, npen, tw);
+    cpx<T>* res = fft_lds<T, false, D == 2>(b0, b1, a.ax, npen, tw);
     const int Hb = a.g.Hb;
     const int nreal = a.rpb * D;
     for (int idx = threadIdx.x; idx < npen * Hb; idx += blockDim.x) {
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(kThreads) void k_middle(MidArgs<T> a)
     for (int c = 0; c < D; c++) where[c] = c;
 #pragma unroll
     for (int c = 0; c < D; c++) {
-        cpx<T>* res = fft_lds<T, false>(reg + where[c] * PL, reg + freebuf * PL, a.ax, P, tw);
+        cpx<T>* res = fft_lds<T, false, D == 2>(reg + where[c] * PL, reg + freebuf * PL, a.ax, P, tw);
         if (res != reg + where[c] * PL) {
             const int t = where[c];
             where[c] = freebuf;
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void k_middle(MidArgs<T> a)
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < D; c++) {
-        cpx<T>* res = fft_lds<T, true>(reg + where[c] * PL, reg + freebuf * PL, a.ax, P, tw);
+        cpx<T>* res = fft_lds<T, true, D == 2>(reg + where[c] * PL, reg + freebuf * PL, a.ax, P, tw);
         if (res != reg + where[c] * PL) {
             const int t = where[c];
             where[c] = freebuf;
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kThreads) void k_last(LastArgs<T> a)
         b0[pen * L + f] = Z;
     }
     __syncthreads();
-    cpx<T>* res = fft_lds<T, true>(b0, b1, a.ax, npen, tw);
+    cpx<T>* res = fft_lds<T, true, D == 2>(b0, b1, a.ax, npen, tw);
     const long long npts = a.g.npts;
     double acc = 0.0;
     for (int idx = threadIdx.x; idx < a.rpb * L; idx += blockDim.x) {
