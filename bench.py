@@ -40,11 +40,10 @@ KINDS = ["first", "axis_fwd", "middle", "axis_inv", "last", "cg_update", "reduce
 # kernels of one CG body on a specialised 3D grid, by launch kind
 CG_KERNELS = {"first": "k2_first<double,3> (x += alpha p, p = r + beta p, A p, r2c of the last axis)",
               "axis_fwd": "k2_axis<double,forward>", "middle": "k2_middle<double,3,G>",
-              "axis_inv": "k2_axis<double,inverse>", "last": "k2_last<double,3,EPI_CG> (c2r, q = C p, (q, p))",
-              "cg_update": "k_cg_update<double> (r -= alpha q, (r, r))", "reduce": "k_reduce"}
+              "axis_inv": "k2_axis<double,inverse>", "last": "k2_last<double,3,EPI_CGR> (c2r, r -= alpha C p, (r, r))", "reduce": "k_reduce"}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_243.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1508_02045_amd", "csrc", f) for f in
-                  ("fgh_kernels.hip", "fgh_fft.hpp", "fgh_internal.hpp", "fgh_v2.hpp", "fgh_args.hpp")]
+                  ("fgh_kernels.hip", "fgh_fft.hpp", "fgh_internal.hpp", "fgh_v2.hpp", "fgh_args.hpp", "fgh_gen.hpp")]
 
 
 def log(msg):
@@ -79,26 +78,14 @@ def apply_bytes(N, p_bytes, a_bytes=1):
     return 2 * F + a_bytes * npts + 2 * S + inner * 2 * S
 
 
-LAST_LEVEL_CACHE_BYTES = 256 * 1024 * 1024
-
-
-def cg_defers(N, p_bytes):
-    """Whether the library's CG leaves x += alpha p to the next body's first pass: when its four
-    vectors exceed the device's 256 MiB last-level cache (the library's rule)."""
-    d, npts, F, S = geometry(N, p_bytes)
-    return 4 * F > LAST_LEVEL_CACHE_BYTES
-
-
 def cg_kind_bytes(N, p_bytes, a_bytes=1):
-    """Algorithmic bytes per launch of each kernel of one CG body (Algorithm 2) with a phase map.
-    With the deferred iterate update (cg_defers): first: x, r, p in, x, p out, phase, spectrum out;
-    update: r, q in, r out.  Otherwise: first: r, p in, p out, phase, spectrum out; update: x, p,
-    r, q in, x, r out.  Strided / middle: spectrum in and out; last: spectrum and p in, q out;
-    reduce: the partial sums."""
+    """Algorithmic bytes per launch of each kernel of one FP64 CG body (Algorithm 2) with a phase map.
+    First: x, r, p in, x, p out, phase, spectrum out; strided / middle: spectrum in and out; last:
+    spectrum and r in, r out; reduce: the partial sums.  (No update kernel: alpha comes from the first
+    pass.)"""
     d, npts, F, S = geometry(N, p_bytes)
-    defer = cg_defers(N, p_bytes)
-    return {"first": (5 if defer else 3) * F + a_bytes * npts + S, "axis_fwd": 2 * S, "middle": 2 * S,
-            "axis_inv": 2 * S, "last": S + 2 * F, "cg_update": (3 if defer else 6) * F, "reduce": 1024 * 8}
+    return {"first": 5 * F + a_bytes * npts + S, "axis_fwd": 2 * S, "middle": 2 * S, "axis_inv": 2 * S,
+            "last": S + 2 * F, "reduce": 1024 * 8}
 
 
 def phase_table(inputs, np, tables):
