@@ -31,11 +31,21 @@ Dense dense_of(const Axis& ax, int lines)
 // One candidate tile: `lines` lines in LDS, `blocks` workgroups in the launch.  The score weighs what
 // bounds a pass: enough workgroups for the 256 compute units (two each), LDS that lets several
 // share one, dense columns in use, and the cache lines of a tile's row segment (seg bytes).
-void consider(GenTile* best, double* score, const Axis& ax, int n, int lines, size_t lds, long long blocks, size_t seg)
+//
+// scarce: no width of the pass gives each unit two workgroups.  A dense step is then scored against
+// one workgroup per unit, and its LDS counts only where it keeps workgroups waiting: one column per
+// workgroup left a third of the 16-wide dense columns empty and shared units unevenly.  FP64 middle
+// pass, before and after: 1023 x 767 41.6 -> 32.0 us (1 -> 2 columns), 999 x 999 44.3 -> 35.6 us.
+// Where two workgroups per unit can be had the rule stays as it was: 93^3 slows from 19.4 to 24.4 us
+// with the other one; so it does for lengths that are one dense step (q = 1), where the other goes
+// either way (667 x 211 166 -> 170 us, 1021 x 1021 352 -> 337 us).
+void consider(GenTile* best, double* score, const Axis& ax, int n, int lines, size_t lds, long long blocks, size_t seg,
+              bool scarce = false)
 {
     if (lds > kLdsMax) return;
     GenTile t{true, n, 0, 0, lds};
-    double s = std::min(1.0, (double)blocks / 512.0);
+    scarce = scarce && ax.p > kGenRadix && ax.q > 1;
+    double s = std::min(1.0, (double)blocks / (scarce ? 256.0 : 512.0));
     if (ax.p <= kGenRadix) {
         if (ax.q * lines > 256) return;  // one step-A subsequence per thread
         t.threads = std::min(256, std::max(64, (std::max(ax.q, ax.p) * lines + 63) / 64 * 64));
@@ -46,7 +56,8 @@ void consider(GenTile* best, double* score, const Axis& ax, int n, int lines, si
         t.threads = 64 * d.waves;
         s *= d.eff;
     }
-    s *= lds <= 40 * 1024 ? 1.0 : lds <= 54 * 1024 ? 0.95 : lds <= 80 * 1024 ? 0.85 : 0.6;
+    if (!scarce || blocks > 256 * (long long)(kLdsMax / lds))
+        s *= lds <= 40 * 1024 ? 1.0 : lds <= 54 * 1024 ? 0.95 : lds <= 80 * 1024 ? 0.85 : 0.6;
     s *= seg >= 128 ? 1.0 : seg >= 64 ? 0.9 : seg >= 32 ? 0.75 : 0.6;
     s *= 1.0 - 0.3 / lines;  // the twiddle table each workgroup loads
     if (s > *score) {
@@ -96,7 +107,8 @@ GenTile gen_mid_tile(const Axis& ax, int cols, size_t cs)
     double score = 0.0;
     for (int P : {16, 12, 8, 7, 6, 5, 4, 3, 2, 1}) {
         if (P > cols) continue;
-        consider(&best, &score, ax, P, 2 * P, (size_t)(ax.L + 2 * (size_t)P * ax.L) * cs, (cols + P - 1) / P, P * cs);
+        consider(&best, &score, ax, P, 2 * P, (size_t)(ax.L + 2 * (size_t)P * ax.L) * cs, (cols + P - 1) / P, P * cs,
+                 cols < 512);
     }
     return best;
 }

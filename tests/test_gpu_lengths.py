@@ -166,3 +166,10 @@ def test_fused_bodies_any_length(N, rule, solver, monkeypatch):
         e.append(x.cpu().numpy())
     plan.close()
     assert np.linalg.norm(e[0] - e[1]) <= 1e-13 * np.sqrt(e[0][0].size)
+
+
+@pytest.mark.parametrize("N", [(93, 3), (999, 257), (1023, 1021), (1023, 1023)])
+def test_apply_few_columns(N):
+    """The dense middle pass where its columns cannot give each unit two workgroups (fewer than 512),
+    from two columns to the first count above that."""
+    test_apply_any_length(N, "phase")
