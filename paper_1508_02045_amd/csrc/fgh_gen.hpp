@@ -13,7 +13,7 @@
 // (subsequences) in four accumulator tiles.  The factors come from the length's own twiddle table
 // in LDS (W_p^m = W_L^{q m}).  The direct sums this replaces ran p^2 dependent table reads per
 // subsequence on one thread.  FP64 application of 201 x 151 x 101 points: 40.2 ms -> 0.406 ms, of
-// 1023 x 767 points: 1.49 ms -> 0.067 ms; a CG body at 85 x 85: 262 -> 32 us.
+// 1023 x 767 points: 1.49 ms -> 0.057 ms; a CG body at 85 x 85: 262 -> 32 us.
 //
 // Every pass keeps its tile in one LDS buffer: a step whose outputs go to other slots than its
 // inputs came from holds the outputs in registers across a barrier (a thread has one step-A
