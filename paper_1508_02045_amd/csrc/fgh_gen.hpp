@@ -71,7 +71,7 @@ __device__ __forceinline__ void step_a_reg(const cpx<T>* src, cpx<T>* dst, int i
     if (act) {
 #pragma unroll
         for (int m = 0; m < R; m++) v[m] = src[m * is];
-        reg_dft<T, R, INV>(v);
+        reg_dft<T, R, INV, true>(v);
     }
     lds_barrier();
     if (act) {
@@ -214,7 +214,7 @@ __device__ __forceinline__ void step_b_reg(cpx<T>* X, const Lines& ln, int p)
         cpx<T> v[R];
 #pragma unroll
         for (int n1 = 0; n1 < R; n1++) v[n1] = y[n1 * p * ln.NS];
-        reg_dft<T, R, INV>(v);
+        reg_dft<T, R, INV, true>(v);
 #pragma unroll
         for (int k1 = 0; k1 < R; k1++) y[k1 * p * ln.NS] = v[k1];
     }
@@ -458,7 +458,7 @@ __device__ __forceinline__ void axis_a_reg(const AxisArgs<T>& a, const cpx<T>* i
             const bool ok = banded ? band_index(s, L, B, &s) : true;
             v[m] = ok ? in[(unsigned)(s * a.inner + j)] : cpx<T>{T(0), T(0)};
         }
-        reg_dft<T, R, INV>(v);
+        reg_dft<T, R, INV, true>(v);
         cpx<T>* y = X + n1 * R * P + col;
 #pragma unroll
         for (int k = 0; k < R; k++) y[k * P] = k ? cmul(v[k], twiddle<T, INV>(tw, n1 * k)) : v[k];
@@ -478,7 +478,7 @@ __device__ __forceinline__ void axis_b_reg(const AxisArgs<T>& a, cpx<T>* out, in
         cpx<T> v[R];
 #pragma unroll
         for (int n1 = 0; n1 < R; n1++) v[n1] = y[n1 * p * P];
-        reg_dft<T, R, INV>(v);
+        reg_dft<T, R, INV, true>(v);
         if (j < a.inner) {
 #pragma unroll
             for (int k1 = 0; k1 < R; k1++) {
@@ -608,8 +608,8 @@ __device__ __forceinline__ void mid_b_reg(const MidArgs<T>& a, int j0, float iP,
             z0[n1] = y[n1 * p * NS];
             zp[n1] = y[n1 * p * NS + P];
         }
-        reg_dft<T, R, false>(z0);
-        reg_dft<T, R, false>(zp);
+        reg_dft<T, R, false, true>(z0);
+        reg_dft<T, R, false, true>(zp);
 #pragma unroll
         for (int k1 = 0; k1 < R; k1++) {
             const int k0 = signed_index(k2 + p * k1, L);
@@ -617,8 +617,8 @@ __device__ __forceinline__ void mid_b_reg(const MidArgs<T>& a, int j0, float iP,
             zp[k1] = kl * t;
             z0[k1] = T(k0) * t;
         }
-        reg_dft<T, R, true>(z0);
-        reg_dft<T, R, true>(zp);
+        reg_dft<T, R, true, true>(z0);
+        reg_dft<T, R, true, true>(zp);
 #pragma unroll
         for (int n1 = 0; n1 < R; n1++) {
             const cpx<T> w = conj(tw[n1 * k2]);
@@ -638,7 +638,7 @@ __device__ __forceinline__ void mid_binv_reg(cpx<T>* X, const Lines& ln, int p, 
         cpx<T> v[R];
 #pragma unroll
         for (int k1 = 0; k1 < R; k1++) v[k1] = y[k1 * p * ln.NS];
-        reg_dft<T, R, true>(v);
+        reg_dft<T, R, true, true>(v);
 #pragma unroll
         for (int n1 = 0; n1 < R; n1++) y[n1 * p * ln.NS] = n1 ? cmul(v[n1], conj(tw[n1 * k2])) : v[n1];
     }
