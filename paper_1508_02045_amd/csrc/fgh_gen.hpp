@@ -10,10 +10,13 @@
 // (h + 1) x (h + 1) products,
 //   X_k, X_{p-k} = sum_m cos(2 pi k m / p) a_m -+ i sum_m sin(2 pi k m / p) b_m,
 // p multiply-adds per point instead of 4 p.  One wavefront computes 16 rows k by 16 columns
-// (subsequences) in four accumulator tiles.  The factors come from the length's own twiddle table
-// in LDS (W_p^m = W_L^{q m}).  The direct sums this replaces ran p^2 dependent table reads per
-// subsequence on one thread.  FP64 application of 201 x 151 x 101 points: 40.2 ms -> 0.406 ms, of
-// 1023 x 767 points: 1.49 ms -> 0.057 ms; a CG body at 85 x 85: 262 -> 32 us.
+// (subsequences) in four accumulator tiles.  Their sums run in two halves: one chain of a composite
+// p rounds more than the short butterflies of its factors (FP64 application at 441 x 441: error
+// 5.3e-16 in one chain, 4.9e-16 in two, 4.9e-16 on the mixed-radix passes; 30.2 -> 30.5 us).  The
+// factors come from the length's own twiddle table in LDS (W_p^m = W_L^{q m}).  The direct sums this
+// replaces ran p^2 dependent table reads per subsequence on one thread.  FP64 application of
+// 201 x 151 x 101 points: 40.2 ms -> 0.406 ms, of 1023 x 767 points: 1.49 ms -> 0.057 ms; a CG body at
+// 85 x 85: 262 -> 32 us.
 //
 // Every pass keeps its tile in one LDS buffer: a step whose outputs go to other slots than its
 // inputs came from holds the outputs in registers across a barrier (a thread has one step-A
@@ -123,22 +126,34 @@ __device__ __forceinline__ void step_a_dense(cpx<T>* X, const Lines& ln, int i1,
                 lo += 4 * is;
                 hi -= 4 * is;
             };
+            auto steps = [&](int n) {
+#pragma unroll 2
+                for (int s = 0; s < n; s++) {
+                    const cpx<T> a = x[lo], b = x[hi];
+                    mac(tw[w], a + b, a - b);
+                }
+            };
             const cpx<T> zero = {T(0), T(0)};
             {   // m = 0 has no mirror (its sine factor is 0)
                 const cpx<T> a = x[lo], b = g ? x[hi] : zero;
                 mac(tw[w], a + b, a - b);
             }
             const int full = (h + 1) >> 2;  // steps whose four m are all <= h
-#pragma unroll 2
-            for (int s = 1; s < full; s++) {
-                const cpx<T> a = x[lo], b = x[hi];
-                mac(tw[w], a + b, a - b);
+            steps((full - 1) >> 1);
+            V half[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                half[u] = acc[i][u];
+                acc[i][u] = V{T(0), T(0), T(0), T(0)};
             }
+            steps(full >> 1);
             if ((h + 1) & 3) {
                 const bool in = 4 * full + g <= h;
                 const cpx<T> a = in ? x[lo] : zero, b = in ? x[hi] : zero;
                 mac(tw[w], a + b, a - b);
             }
+#pragma unroll
+            for (int u = 0; u < 4; u++) acc[i][u] += half[u];
         }
     }
     lds_barrier();

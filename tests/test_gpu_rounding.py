@@ -43,3 +43,13 @@ def error(N, dtype):
 def test_register_radices(N, mixed):
     """Products of two register radices, 9 to 17 among them, in double precision."""
     assert error(N, np.float64) <= 1.02 * mixed
+
+
+@pytest.mark.parametrize("N,mixed64,mixed32", [((441, 441), 4.868e-16, 2.485e-07), ((525, 525), 4.559e-16, 2.371e-07),
+                                               ((945, 945), 5.074e-16, 2.701e-07), ((999, 999), 6.613e-16, 3.107e-07),
+                                               ((1023, 767), 6.103e-16, 3.247e-07), ((511, 509), 1.174e-15, 6.331e-07),
+                                               ((201, 151, 101), 8.954e-16, 4.803e-07)])
+def test_dense_steps(N, mixed64, mixed32):
+    """Dense steps of composite length (49, 35, 63, 111, 93) and of prime length, in both precisions."""
+    assert error(N, np.float64) <= 1.02 * mixed64
+    assert error(N, np.float32) <= 1.02 * mixed32
