@@ -53,3 +53,12 @@ def test_dense_steps(N, mixed64, mixed32):
     """Dense steps of composite length (49, 35, 63, 111, 93) and of prime length, in both precisions."""
     assert error(N, np.float64) <= 1.02 * mixed64
     assert error(N, np.float32) <= 1.02 * mixed32
+
+
+@pytest.mark.parametrize("N,mixed", [((51, 51), 2.222e-07), ((75, 75), 2.079e-07), ((105, 105), 2.068e-07),
+                                     ((225, 225), 2.267e-07), ((375, 375), 2.488e-07), ((127, 129), 3.597e-07),
+                                     ((1021, 1021), 1.150e-06), ((75, 75, 75), 2.445e-07), ((105, 105, 105), 2.456e-07),
+                                     ((89, 97, 101), 4.531e-07)])
+def test_single_precision(N, mixed):
+    """Smooth and prime lengths in single precision, whose multiplier weights are formed in it."""
+    assert error(N, np.float32) <= 1.02 * mixed
