@@ -34,7 +34,7 @@ size_t lds_budget()
     const char* v = std::getenv("FGH_LDS_BUDGET");
     if (v) {
         const long b = std::atol(v);
-        if (b >= 8192 && b <= 160 * 1024) return (size_t)b;
+        if (b >= 8192 && b <= (long)kLdsPerUnit) return std::min((size_t)b, kLdsPerUnit - kLdsStatic);
     }
     return kLdsBudgetDefault;
 }
@@ -215,9 +215,9 @@ void use_run_time_lengths(const Geo& g, size_t cs, size_t rs, Config* c)
 {
     const int d = g.d;
     const long long span = (long long)d * std::max(g.npts, std::max(g.s1, g.s2));
-    const size_t tabb = kMaxPhases * 6 * rs, max_lds = 160 * 1024;
+    const size_t tabb = kMaxPhases * 6 * rs;
     auto fits = [&](int L, size_t lines) {
-        return span < (1LL << 31) && (L + lines * (size_t)L) * cs + tabb <= max_lds;
+        return span < (1LL << 31) && (L + lines * (size_t)L) * cs + tabb + kLdsStatic <= kLdsPerUnit;
     };
     Axis ax[3];
     for (int a = 0; a < d; a++) split_length(ax[a].L = g.L[a], &ax[a]);

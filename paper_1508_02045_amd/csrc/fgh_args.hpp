@@ -90,6 +90,7 @@ struct Pending {
     int nend, npq;
     // workgroups before those of the tiles: one per XCD, so that a tile's XCD stays that of its rank
     static constexpr int kBlocks = 8;
+    static constexpr size_t kLds = 2 * (kThreads / 64) * sizeof(double);  // dynamic LDS the sums take
     __host__ __device__ int blocks() const { return sc ? kBlocks : 0; }
 };
 

@@ -334,7 +334,8 @@ __device__ __forceinline__ void load_half_spectra(const Geo& g, int L, const cpx
 template <typename T, int D, int NI>
 __global__ __launch_bounds__(kGenMaxThreads) void kg_first(FirstArgs<T> a, int op)
 {
-    __shared__ double red[2 * kGenMaxThreads / 64];
+    static_assert(kGenMaxThreads >= 2 * kThreads, "first_beta's sums share the block sum's doubles");
+    __shared__ double red[kGenMaxThreads / 64];
     T beta = T(0);
     if (!a.end_part && a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];

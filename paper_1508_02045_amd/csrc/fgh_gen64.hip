@@ -9,8 +9,6 @@ FGH_GEN_INSTANTIATE(double)
 
 namespace {
 
-constexpr size_t kLdsMax = 160 * 1024;
-
 // Dense products of a tile of `lines` lines of length q p, and the wavefronts that share them.
 struct Dense {
     int items, ni, waves;
@@ -42,7 +40,7 @@ Dense dense_of(const Axis& ax, int lines)
 void consider(GenTile* best, double* score, const Axis& ax, int n, int lines, size_t lds, long long blocks, size_t seg,
               bool scarce = false)
 {
-    if (lds > kLdsMax) return;
+    if (lds + kLdsStatic > kLdsPerUnit) return;
     GenTile t{true, n, 0, 0, lds};
     scarce = scarce && ax.p > kGenRadix && ax.q > 1;
     double s = std::min(1.0, (double)blocks / (scarce ? 256.0 : 512.0));
@@ -56,7 +54,7 @@ void consider(GenTile* best, double* score, const Axis& ax, int n, int lines, si
         t.threads = 64 * d.waves;
         s *= d.eff;
     }
-    if (!scarce || blocks > 256 * (long long)(kLdsMax / lds))
+    if (!scarce || blocks > 256 * (long long)(kLdsPerUnit / lds))
         s *= lds <= 40 * 1024 ? 1.0 : lds <= 54 * 1024 ? 0.95 : lds <= 80 * 1024 ? 0.85 : 0.6;
     s *= seg >= 128 ? 1.0 : seg >= 64 ? 0.9 : seg >= 32 ? 0.75 : 0.6;
     s *= 1.0 - 0.3 / lines;  // the twiddle table each workgroup loads

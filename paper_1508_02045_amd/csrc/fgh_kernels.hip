@@ -1382,6 +1382,7 @@ static hipError_t build_bundle_d(const OpPlan& op, const ApplyArgs& a, ApplyBund
     fa.nend = nend;
     const Pending pend = {a.defer_redop >= 0 || a.cg_pq == 2 ? op.sc : nullptr, a.end_part, op.partials2, nend,
                           a.cg_pq == 2 ? (int)bu->nblk1 : 0};
+    if (pend.sc && (D == 3 ? op.lds_axis : op.lds_mid) < Pending::kLds) return hipErrorInvalidValue;
     const int* done = a.loop ? &op.sc->done : nullptr;
     fa.done = done;
     for (int c = 0; c < 3; c++) fa.E[c] = a.E[c];

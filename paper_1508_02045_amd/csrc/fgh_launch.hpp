@@ -122,6 +122,11 @@ inline unsigned axis_blocks(const AxisArgs<T>& a)
     return (unsigned)((long long)a.ntiles * a.outer * a.comps + a.pend.blocks());
 }
 
+// LDS of a compute unit, and the part of it that a pass kernel declares by itself beside its dynamic
+// tile (at most: its block sum's doubles).  A tile that takes all of it cannot be launched.
+constexpr size_t kLdsPerUnit = 160 * 1024;
+constexpr size_t kLdsStatic = 64;
+
 // Tile of a run-time-length pass: rows per block or columns per tile, threads, dense products per
 // wavefront and LDS bytes; ok = false where the mixed-radix passes are used.
 struct GenTile {

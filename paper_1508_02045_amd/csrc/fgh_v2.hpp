@@ -137,11 +137,13 @@ __device__ __forceinline__ double sum_partials(const double* p, int n, double* r
 // the first does it).  The partial sums were written by
 // earlier kernels, so no fence or counter is needed.  Same summation order and scalar update as
 // the separate reduction kernel.  The sums are taken whether or not an end is pending, so that their
-// loads do not wait for the flag.
+// loads do not wait for the flag.  The sums use the tile's LDS (Pending::kLds bytes of it at least),
+// so that the tiles' workgroups declare none beside it.
 __device__ __forceinline__ void finish_pending(const Pending& p, int b)
 {
     if (b) return;
-    __shared__ double red[2 * kThreads / 64];
+    extern __shared__ __align__(16) unsigned char smem[];
+    double* red = reinterpret_cast<double*>(smem);
     Scalars* s = p.sc;
     double end, pq;
     sum_partials2(p.end, p.nend, p.pq, p.npq, red, &end, &pq);
