@@ -480,6 +480,7 @@ void fill_opplan_at(OpPlan* op, const Geo& g, bool f32, char* const tw[3], char*
 // Switches an operator description to the run-time-length passes where they apply.
 void set_run_time_lengths(OpPlan* op, bool f32)
 {
+    if (op->v2_row && op->v2_mid && (op->g.d == 2 || op->v2_axis)) return;
     Config c = choose_config(op->g, f32 ? 8 : 16, f32 ? 4 : 8);
     use_run_time_lengths(op->g, f32 ? 8 : 16, f32 ? 4 : 8, &c);
     if (c.row.ok) {
@@ -2563,16 +2564,18 @@ fgh_status fgh_plan_bounds(fgh_plan p, double* c_A, double* C_A)
     return FGH_OK;
 }
 
-// The operator of a plain application: the passes chosen at plan creation with the plan's current
-// stream, coefficients and profiler.
-static OpPlan apply_plan(fgh_plan p, bool f32)
+// The operator of a plain application: the solves' own, or, on a refined plan with run-time lengths,
+// the passes chosen at plan creation with the plan's current stream, coefficients and profiler (in *buf).
+static const OpPlan& apply_plan(fgh_plan p, bool f32, OpPlan* buf)
 {
     const OpPlan& s = f32 ? p->op32 : p->op64;
-    OpPlan op = f32 ? p->ap32 : p->ap64;
-    op.stream = s.stream;
-    op.A = s.A;
-    op.prof = s.prof;
-    return op;
+    const OpPlan& ap = f32 ? p->ap32 : p->ap64;
+    if (p->prec == FGH_FP64 || !(ap.gen_row || ap.gen_axis || ap.gen_mid)) return s;
+    *buf = ap;
+    buf->stream = s.stream;
+    buf->A = s.A;
+    buf->prof = s.prof;
+    return *buf;
 }
 
 fgh_status fgh_apply(fgh_plan p, const double* x, double* y)
@@ -2585,7 +2588,8 @@ fgh_status fgh_apply(fgh_plan p, const double* x, double* y)
     a.sgn = 1.0;
     a.y = y;
     int nb = 0;
-    HIPOK(run_apply<double>(apply_plan(p, false), a, &nb));
+    OpPlan buf;
+    HIPOK(run_apply<double>(apply_plan(p, false, &buf), a, &nb));
     return FGH_OK;
 }
 
@@ -2600,7 +2604,8 @@ fgh_status fgh_apply_f32(fgh_plan p, const float* x, float* y)
     a.sgn = 1.0;
     a.y = y;
     int nb = 0;
-    HIPOK(run_apply<float>(apply_plan(p, true), a, &nb));
+    OpPlan buf;
+    HIPOK(run_apply<float>(apply_plan(p, true, &buf), a, &nb));
     return FGH_OK;
 }
 

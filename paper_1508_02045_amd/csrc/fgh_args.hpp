@@ -97,9 +97,6 @@ struct Pending {
 template <typename T>
 struct FirstArgs {
     const int* done;  // the loop's stop flag (nullptr: always run)
-    // OP_AP_CG: the nend partial sums of the previous body's (r, r), read while its end is pending
-    // (Scalars::pend; nullptr: beta is in the scalar block)
-    const double* end_part;
     Geo g;
     Axis ax;
     int rpb, npen;
@@ -110,19 +107,21 @@ struct FirstArgs {
     // p on entry, before p is replaced (nullptr: x is updated elsewhere)
     T* xd;
     const Scalars* sc;
-    int nend;
-    double* pq_part;  // OP_AP_CG: the partial sums of (A p, p), one per workgroup (nullptr: not wanted)
     double E[3];
     double omega;
     CoefArgs A;
     cpx<T>* out;
     const cpx<T>* twg;
+    // OP_AP_CG: the nend partial sums of the previous body's (r, r), read while its end is pending
+    // (Scalars::pend; nullptr: beta is in the scalar block)
+    const double* end_part;
+    int nend;
+    double* pq_part;  // OP_AP_CG: the partial sums of (A p, p), one per workgroup (nullptr: not wanted)
 };
 
 template <typename T>
 struct AxisArgs {
     const int* done;  // the loop's stop flag (nullptr: always run)
-    Pending pend;     // loop reductions left to this pass
     Axis ax;
     int nin, nout;          // stored counts along the axis
     int bin, bout;          // 1: stored index is a band index (frequency signed(s, n)), 0: position
@@ -132,12 +131,12 @@ struct AxisArgs {
     cpx<T>* out;
     const cpx<T>* twg;
     int outer, comps;         // the launch: ntiles x outer x comps workgroups, after pend's
+    Pending pend;             // loop reductions left to this pass
 };
 
 template <typename T>
 struct MidArgs {
     const int* done;  // the loop's stop flag (nullptr: always run)
-    Pending pend;     // 2D: loop reductions left to this pass (its workgroups precede the ntiles of the pass)
     Axis ax;
     int B0, cols, Hb, B1, P, ntiles;
     int ys;        // specialised kernel: LDS stride of a column (complex elements, >= L)
@@ -145,6 +144,7 @@ struct MidArgs {
     double scale;  // 1 / |grid| (the forward DFT factor of eq:DFT)
     cpx<T>* buf;
     const cpx<T>* twg;
+    Pending pend;  // 2D: loop reductions left to this pass (its workgroups precede the ntiles of the pass)
 };
 
 template <typename T>

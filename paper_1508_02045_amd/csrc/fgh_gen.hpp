@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kGenMaxThreads) void kg_first(FirstArgs<T> a, int o
     static_assert(kGenMaxThreads >= 2 * kThreads, "first_beta's sums share the block sum's doubles");
     __shared__ double red[kGenMaxThreads / 64];
     T beta = T(0);
-    if (!a.end_part && a.done && *a.done) return;
+    if (!(op == OP_AP_CG && a.end_part) && a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, npen = a.npen;
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
@@ -510,7 +510,7 @@ template <typename T, bool INV, int NI>
 __global__ __launch_bounds__(kGenMaxThreads) void kg_axis(AxisArgs<T> a, int B)
 {
     int b = blockIdx.x;
-    if (a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
+    if (!INV && a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, P = a.P, q = a.ax.q, p = a.ax.p;

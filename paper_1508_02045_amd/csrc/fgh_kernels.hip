@@ -23,7 +23,7 @@ __global__ __launch_bounds__(kThreads) void k_first(FirstArgs<T> a)
 {
     __shared__ double red[2 * kThreads / 64];
     T beta = T(0);
-    if (!a.end_part && a.done && *a.done) return;
+    if (!(OP == OP_AP_CG && a.end_part) && a.done && *a.done) return;
     if (OP == OP_AP_CG && !first_beta(a, red, &beta)) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L;
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kThreads) void k_first(FirstArgs<T> a)
                 b0[(pp >> 1) * L + i].x = z[c];
         }
     }
-    if (sizeof(T) == 8 && a.pq_part) {
+    if (OP == OP_AP_CG && sizeof(T) == 8 && a.pq_part) {
         const double tot = block_sum(acc, red);
         if (threadIdx.x == 0) a.pq_part[blockIdx.x] = tot;
     }
@@ -129,7 +129,7 @@ template <typename T, bool INV>
 __global__ __launch_bounds__(kThreads) void k_axis(AxisArgs<T> a)
 {
     int b = blockIdx.x;
-    if (a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
+    if (!INV && a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L;
@@ -1120,8 +1120,13 @@ static hipError_t v2_first(const OpPlan& op, const FirstArgs<T>& fa, int opc, un
 {
     const size_t lds = fa.xd ? op.lds_first_x : op.lds_first_v2;
     switch (fa.ax.L) {
-#define C(LL, A1, A2) \
-    case LL: LAUNCH_LDS((k2_first<T, D, A1, A2>), dim3(nblk), lds, op.stream, fa, opc); break;
+#define C(LL, A1, A2)                                                                                  \
+    case LL:                                                                                           \
+        if (opc == OP_AP_CG)                                                                           \
+            LAUNCH_LDS((k2_first<T, D, A1, A2, true>), dim3(nblk), lds, op.stream, fa, opc);           \
+        else                                                                                           \
+            LAUNCH_LDS((k2_first<T, D, A1, A2, false>), dim3(nblk), lds, op.stream, fa, opc);          \
+        break;
         V2_ROW_CASES(C)
 #undef C
         default: return hipErrorInvalidValue;
@@ -1192,23 +1197,31 @@ static hipError_t v2_lastfirst(const OpPlan& op, const LastArgs<T>& la, int epi,
     return hipErrorInvalidValue;
 }
 
-template <typename T, int D>
-static hipError_t v2_middle(const OpPlan& op, const MidArgs<T>& ma, int mult)
+template <typename T, int D, bool PEND>
+static hipError_t v2_middle_p(const OpPlan& op, const MidArgs<T>& ma, int mult)
 {
     const size_t lds = op.lds_mid;
+    const dim3 grid(ma.ntiles + ma.pend.blocks());
     switch (ma.ax.L) {
 #define C(LL, A1, A2)                                                                          \
     case LL:                                                                                   \
         if (mult == MULT_G)                                                                    \
-            LAUNCH_LDS((k2_middle<T, D, A1, A2, MULT_G>), dim3(ma.ntiles + ma.pend.blocks()), lds, op.stream, ma);  \
+            LAUNCH_LDS((k2_middle<T, D, A1, A2, MULT_G, PEND>), grid, lds, op.stream, ma);     \
         else                                                                                   \
-            LAUNCH_LDS((k2_middle<T, D, A1, A2, MULT_EM>), dim3(ma.ntiles + ma.pend.blocks()), lds, op.stream, ma); \
+            LAUNCH_LDS((k2_middle<T, D, A1, A2, MULT_EM, PEND>), grid, lds, op.stream, ma);    \
         break;
         V2_COL_CASES(C)
 #undef C
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+template <typename T, int D>
+static hipError_t v2_middle(const OpPlan& op, const MidArgs<T>& ma, int mult)
+{
+    if constexpr (D == 2)
+        if (ma.pend.sc) return v2_middle_p<T, D, true>(op, ma, mult);
+    return v2_middle_p<T, D, false>(op, ma, mult);
 }
 
 template <typename T>
@@ -1220,9 +1233,11 @@ static hipError_t v2_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int
 #define C(LL, A1, A2)                                                                        \
     case LL:                                                                                 \
         if (inv)                                                                             \
-            LAUNCH_LDS((k2_axis<T, A1, A2, true>), grid, lds, op.stream, xa, B);             \
+            LAUNCH_LDS((k2_axis<T, A1, A2, true, false>), grid, lds, op.stream, xa, B);      \
+        else if (xa.pend.sc)                                                                 \
+            LAUNCH_LDS((k2_axis<T, A1, A2, false, true>), grid, lds, op.stream, xa, B);      \
         else                                                                                 \
-            LAUNCH_LDS((k2_axis<T, A1, A2, false>), grid, lds, op.stream, xa, B);            \
+            LAUNCH_LDS((k2_axis<T, A1, A2, false, false>), grid, lds, op.stream, xa, B);     \
         break;
         V2_COL_CASES(C)
 #undef C
@@ -1240,7 +1255,10 @@ static hipError_t v2_first_b(const OpPlan& op, const FirstArgs<T>* tab, int opc,
     switch (op.ax[D - 1].L) {
 #define C(LL, A1, A2)                                                                   \
     case LL:                                                                            \
-        LAUNCH_LDS((k2_first_b<T, D, A1, A2>), grid, lds, op.stream, tab, opc);         \
+        if (opc == OP_AP_CG)                                                            \
+            LAUNCH_LDS((k2_first_b<T, D, A1, A2, true>), grid, lds, op.stream, tab, opc);  \
+        else                                                                            \
+            LAUNCH_LDS((k2_first_b<T, D, A1, A2, false>), grid, lds, op.stream, tab, opc); \
         break;
         V2_ROW_CASES(C)
 #undef C
@@ -1283,7 +1301,7 @@ static hipError_t v2_last_b(const OpPlan& op, const LastArgs<T>* tab, int epi, b
     return hipGetLastError();
 }
 
-template <typename T, int D>
+template <typename T, int D, bool PEND>
 static hipError_t v2_middle_b(const OpPlan& op, const MidArgs<T>* tab, int mult, int blocks, int nb)
 {
     const size_t lds = op.lds_mid;
@@ -1292,9 +1310,9 @@ static hipError_t v2_middle_b(const OpPlan& op, const MidArgs<T>* tab, int mult,
 #define C(LL, A1, A2)                                                                          \
     case LL:                                                                                   \
         if (mult == MULT_G)                                                                    \
-            LAUNCH_LDS((k2_middle_b<T, D, A1, A2, MULT_G>), grid, lds, op.stream, tab);        \
+            LAUNCH_LDS((k2_middle_b<T, D, A1, A2, MULT_G, PEND>), grid, lds, op.stream, tab);  \
         else                                                                                   \
-            LAUNCH_LDS((k2_middle_b<T, D, A1, A2, MULT_EM>), grid, lds, op.stream, tab);       \
+            LAUNCH_LDS((k2_middle_b<T, D, A1, A2, MULT_EM, PEND>), grid, lds, op.stream, tab); \
         break;
         V2_COL_CASES(C)
 #undef C
@@ -1304,7 +1322,7 @@ static hipError_t v2_middle_b(const OpPlan& op, const MidArgs<T>* tab, int mult,
 }
 
 template <typename T>
-static hipError_t v2_axis_b(const OpPlan& op, const AxisArgs<T>* tab, bool inv, int blocks, int B, int nb)
+static hipError_t v2_axis_b(const OpPlan& op, const AxisArgs<T>* tab, bool inv, bool pend, int blocks, int B, int nb)
 {
     const dim3 grid(blocks, nb);
     const size_t lds = op.lds_axis;
@@ -1312,9 +1330,11 @@ static hipError_t v2_axis_b(const OpPlan& op, const AxisArgs<T>* tab, bool inv, 
 #define C(LL, A1, A2)                                                                           \
     case LL:                                                                                    \
         if (inv)                                                                                \
-            LAUNCH_LDS((k2_axis_b<T, A1, A2, true>), grid, lds, op.stream, tab, B);     \
+            LAUNCH_LDS((k2_axis_b<T, A1, A2, true, false>), grid, lds, op.stream, tab, B);      \
+        else if (pend)                                                                          \
+            LAUNCH_LDS((k2_axis_b<T, A1, A2, false, true>), grid, lds, op.stream, tab, B);      \
         else                                                                                    \
-            LAUNCH_LDS((k2_axis_b<T, A1, A2, false>), grid, lds, op.stream, tab, B);    \
+            LAUNCH_LDS((k2_axis_b<T, A1, A2, false, false>), grid, lds, op.stream, tab, B);     \
         break;
         V2_COL_CASES(C)
 #undef C
@@ -1812,9 +1832,15 @@ static hipError_t apply_batch_d(const OpPlan& op, const ApplyBundle<T>& b0, cons
     hipError_t e;
     if (!b0.skip_first && (e = v2_first_b<T, D>(op, t.fa, b0.op, b0.nblk1, nb)) != hipSuccess) return e;
     if (b0.first_only) return hipSuccess;
-    if (D == 3 && (e = v2_axis_b<T>(op, t.xf, false, axis_blocks(b0.xf), g.B[1], nb)) != hipSuccess) return e;
-    if ((e = v2_middle_b<T, D>(op, t.ma, b0.mult, b0.ma.ntiles + b0.ma.pend.blocks(), nb)) != hipSuccess) return e;
-    if (D == 3 && (e = v2_axis_b<T>(op, t.xi, true, axis_blocks(b0.xi), g.B[1], nb)) != hipSuccess) return e;
+    if (D == 3 && (e = v2_axis_b<T>(op, t.xf, false, b0.xf.pend.sc, axis_blocks(b0.xf), g.B[1], nb)) != hipSuccess)
+        return e;
+    const int mb = b0.ma.ntiles + b0.ma.pend.blocks();
+    if constexpr (D == 2)
+        e = b0.ma.pend.sc ? v2_middle_b<T, D, true>(op, t.ma, b0.mult, mb, nb) : v2_middle_b<T, D, false>(op, t.ma, b0.mult, mb, nb);
+    else
+        e = v2_middle_b<T, D, false>(op, t.ma, b0.mult, mb, nb);
+    if (e != hipSuccess) return e;
+    if (D == 3 && (e = v2_axis_b<T>(op, t.xi, true, false, axis_blocks(b0.xi), g.B[1], nb)) != hipSuccess) return e;
     return v2_last_b<T, D>(op, t.la, b0.epi, b0.fused, b0.nblk_last, nb);
 }
 

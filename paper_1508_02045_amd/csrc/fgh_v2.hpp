@@ -856,10 +856,15 @@ __device__ __forceinline__ void first_transform_store_ip(const Args& a, long lon
 
 // First pass with one LDS buffer of npairs packed rows (the stages run in place).
 // LDS: twiddles | Zc (npairs complex rows) | phase table.
-template <typename T, int D, int L1, int L2, int KU = FirstTune<T, L1 * L2>::ku, int KX = FirstTune<T, L1 * L2>::kx>
+// CG: op is OP_AP_CG.  A first pass of its own: the tests for beta, the pending end and the sums are
+// a chain of scalar loads that a plain application's pass would wait for (FP32 applications of 63^2 and
+// 45^3 points with a pass for both and one for each: 15.12 and 15.00, 25.91 and 25.72 us).
+template <typename T, int D, int L1, int L2, bool CG, int KU = FirstTune<T, L1 * L2>::ku,
+          int KX = FirstTune<T, L1 * L2>::kx>
 __device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, int b, int nb)
 {
-    if (!a.end_part && a.done && *a.done) return;
+    __builtin_assume(CG == (op == OP_AP_CG));
+    if (!(CG && a.end_part) && a.done && *a.done) return;
     constexpr int L = L1 * L2;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[2 * kThreads / 64];
@@ -867,15 +872,13 @@ __device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, int b,
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* Zc = tw + L;
     T* tab = reinterpret_cast<T*>(Zc + npairs * L);
-    TwiddleCopy<T, L> tc;
-    tc.load(a.twg);
+    for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
     if (a.A.kind == AK_PHASE)
         for (int m = threadIdx.x; m < kMaxPhases * 6; m += blockDim.x) tab[m] = T(a.A.tab[m / 6][m % 6]);
-    tc.store(tw);
     if ((a.rpb * D) & 1)  // the imaginary half of the last packed row is a zero row
         for (int i = threadIdx.x; i < L; i += blockDim.x) Zc[(npairs - 1) * L + i].y = T(0);
     T beta = T(0);
-    if (op == OP_AP_CG && !first_beta(a, red, &beta)) return;
+    if (CG && !first_beta(a, red, &beta)) return;
     lds_barrier();
     const long long row0 = xcd_tile(b, nb) * a.rpb;
     double acc = 0.0;
@@ -885,7 +888,7 @@ __device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, int b,
         const long long left = a.g.rows * (long long)L - pt0;
         const int lim = left < total ? (int)left : total;
         T* Zr = reinterpret_cast<T*>(Zc);
-        if (op == OP_AP_CG && a.xd) {
+        if (CG && a.xd) {
             for (int base = 0; base < total; base += KX * blockDim.x)
                 first_stage0_chunk<T, D, L, KX, true>(a, op, tab, beta, base, total, lim, pt0, Zr, RowLen<L>{}, L, acc);
         } else {
@@ -893,7 +896,7 @@ __device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, int b,
                 first_stage0_chunk<T, D, L, KU>(a, op, tab, beta, base, total, lim, pt0, Zr, RowLen<L>{}, L, acc);
         }
     }
-    if (sizeof(T) == 8 && a.pq_part) {
+    if (CG && sizeof(T) == 8 && a.pq_part) {
         const double tot = block_sum(acc, red);
         if (threadIdx.x == 0) a.pq_part[b] = tot;
     }
@@ -901,19 +904,19 @@ __device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, int b,
     first_transform_store_ip<T, D, L1, L2>(a, row0, tw, Zc);
 }
 
-template <typename T, int D, int L1, int L2>
+template <typename T, int D, int L1, int L2, bool CG>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k2_first(FirstArgs<T> a, int op)
 {
-    first_body<T, D, L1, L2>(a, op, blockIdx.x, gridDim.x);
+    first_body<T, D, L1, L2, CG>(a, op, blockIdx.x, gridDim.x);
 }
 
 // Several plans of one shape in one launch: member blockIdx.y with its own argument block; the
 // member's workgroups see the block ids and tile mapping of the single-plan launch.
-template <typename T, int D, int L1, int L2>
+template <typename T, int D, int L1, int L2, bool CG>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k2_first_b(
     const FirstArgs<T>* __restrict__ tab, int op)
 {
-    first_body<T, D, L1, L2>(tab[blockIdx.y], op, blockIdx.x, gridDim.x);
+    first_body<T, D, L1, L2, CG>(tab[blockIdx.y], op, blockIdx.x, gridDim.x);
 }
 
 // Step-A jobs of the strided pass: load a subsequence and transform it, then write it to LDS times its
@@ -948,11 +951,11 @@ __device__ __forceinline__ void run_jobs(int n, FT table, FL load_transform, FX 
 // Strided axis pass (3D axis 1), one component per workgroup, tile of P columns.
 // ------------------------------------------------------------------------------------------
 // b: the workgroup's linear id over the (tile, outer, component) grid of one plan, after that of the
-// pending loop reductions.
-template <typename T, int L1, int L2, bool INV>
+// pending loop reductions (PEND: a.pend.sc is set; a kernel of its own, see first_body).
+template <typename T, int L1, int L2, bool INV, bool PEND>
 __device__ __forceinline__ void axis_body(const AxisArgs<T>& a, int B, int b)
 {
-    if (a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
+    if (PEND && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     const int gx = a.ntiles, gy = a.outer;
     constexpr int L = L1 * L2;
@@ -1022,27 +1025,27 @@ __device__ __forceinline__ void axis_body(const AxisArgs<T>& a, int B, int b)
     }
 }
 
-template <typename T, int L1, int L2, bool INV>
+template <typename T, int L1, int L2, bool INV, bool PEND>
 __global__ __launch_bounds__(kThreads) void k2_axis(AxisArgs<T> a, int B)
 {
-    axis_body<T, L1, L2, INV>(a, B, blockIdx.x);
+    axis_body<T, L1, L2, INV, PEND>(a, B, blockIdx.x);
 }
 
 // Several plans of one shape: member blockIdx.y.
-template <typename T, int L1, int L2, bool INV>
+template <typename T, int L1, int L2, bool INV, bool PEND>
 __global__ __launch_bounds__(kThreads) void k2_axis_b(const AxisArgs<T>* __restrict__ tab, int B)
 {
-    axis_body<T, L1, L2, INV>(tab[blockIdx.y], B, blockIdx.x);
+    axis_body<T, L1, L2, INV, PEND>(tab[blockIdx.y], B, blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
 // Middle pass along axis 0 (all components, in place): forward step A -> LDS -> forward step B,
 // multiplier and inverse step B in registers -> LDS -> inverse step A.
 // ------------------------------------------------------------------------------------------
-template <typename T, int D, int L1, int L2, int MULT>
+template <typename T, int D, int L1, int L2, int MULT, bool PEND>
 __device__ __forceinline__ void middle_body(const MidArgs<T>& a, int b)
 {
-    if (D == 2 && a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
+    if (PEND && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     constexpr int L = L1 * L2;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1204,16 +1207,16 @@ __device__ __forceinline__ void middle_body(const MidArgs<T>& a, int b)
     }
 }
 
-template <typename T, int D, int L1, int L2, int MULT>
+template <typename T, int D, int L1, int L2, int MULT, bool PEND>
 __global__ __launch_bounds__(kThreads) void k2_middle(MidArgs<T> a)
 {
-    middle_body<T, D, L1, L2, MULT>(a, blockIdx.x);
+    middle_body<T, D, L1, L2, MULT, PEND>(a, blockIdx.x);
 }
 
-template <typename T, int D, int L1, int L2, int MULT>
+template <typename T, int D, int L1, int L2, int MULT, bool PEND>
 __global__ __launch_bounds__(kThreads) void k2_middle_b(const MidArgs<T>* __restrict__ tab)
 {
-    middle_body<T, D, L1, L2, MULT>(tab[blockIdx.y], blockIdx.x);
+    middle_body<T, D, L1, L2, MULT, PEND>(tab[blockIdx.y], blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1322,8 +1325,9 @@ __device__ __forceinline__ void last_body(const LastArgs<T>& a, int b, int nb)
     T* tab = reinterpret_cast<T*>(Sx + npairs * (L + 1));
     __shared__ double red[kThreads / 64];
     // the twiddles share the spectra's memory latency in single precision (243^3: 81 -> 77 us); in
-    // double the registers they wait in cost more (125^3: 26.4 -> 27.8 us)
-    constexpr bool late = sizeof(T) == 4;
+    // double the registers they wait in cost more (125^3: 26.4 -> 27.8 us), and on the few rows of a 2D
+    // grid there is nothing to gain (63^2 FP32 application 15.06 -> 14.95 us without)
+    constexpr bool late = sizeof(T) == 4 && D == 3;
     TwiddleCopy<T, L> tc;
     tc.load(a.twg);
     if (!late) tc.store(tw);
