@@ -81,11 +81,12 @@ def apply_bytes(N, p_bytes, a_bytes=1):
 def cg_kind_bytes(N, p_bytes, a_bytes=1):
     """Algorithmic bytes per launch of each kernel of one FP64 CG body (Algorithm 2) with a phase map.
     First: x, r, p in, x, p out, phase, spectrum out; strided / middle: spectrum in and out; last:
-    spectrum and r in, r out; reduce: the partial sums.  (No update kernel: alpha comes from the first
-    pass.)"""
+    spectrum and r in, r out; reduce: one partial sum per tile of the last pass (eight rows).  (No
+    update kernel: alpha comes from the first pass.)"""
     d, npts, F, S = geometry(N, p_bytes)
+    tiles = (npts // N[-1] + 7) // 8
     return {"first": 5 * F + a_bytes * npts + S, "axis_fwd": 2 * S, "middle": 2 * S, "axis_inv": 2 * S,
-            "last": S + 2 * F, "reduce": 1024 * 8}
+            "last": S + 2 * F, "reduce": 8 * tiles}
 
 
 def phase_table(inputs, np, tables):
