@@ -210,7 +210,8 @@ Config choose_config(const Geo& g, size_t cs /* bytes per complex */, size_t rs 
 // They serve fgh_apply, fgh_apply_f32 and double-precision solves.  Refined solves keep the
 // mixed-radix passes in both precisions: the rounding of an inner solve enters a refined result at
 // about 1e-8 of it (the outer loop stops at the caller's tolerance), where the residual is rounded
-// to single precision too, and those results stay what they have been.
+// to single precision too, and their transforms and iterates stay what they have been.  (Fewer rows
+// per block regroup a loop's partial sums, which shows in the last digits of the test quantity.)
 void use_run_time_lengths(const Geo& g, size_t cs, size_t rs, Config* c)
 {
     const int d = g.d;

@@ -5,9 +5,10 @@
 // multiplies by the twiddles exp(-+2 pi i (j mod Ns) r / (Ns R)), applies the radix-R DFT and
 // writes outputs at (j - j mod Ns) R + j mod Ns + r Ns into the other LDS buffer (Stockham
 // auto-sort: no bit reversal, natural order in and out).  Radices 3, 5, 7 use closed-form
-// butterflies with compile-time roots; any other odd prime uses a direct sum whose roots come
-// from the twiddle table.  All lengths on the hot path (63, 125, 135, 243, 45, 81, 729) factor
-// into 3, 5 and 7.
+// butterflies with compile-time roots; any other odd prime uses direct sums whose roots come from
+// the twiddle table, one butterfly per thread (3D) or one output per thread (2D).  These transforms
+// serve refined solves at lengths without a specialised kernel and what the run-time-length passes
+// do not take.
 #pragma once
 #include <hip/hip_runtime.h>
 
