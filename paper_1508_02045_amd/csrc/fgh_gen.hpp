@@ -10,13 +10,14 @@
 // (h + 1) x (h + 1) products,
 //   X_k, X_{p-k} = sum_m cos(2 pi k m / p) a_m -+ i sum_m sin(2 pi k m / p) b_m,
 // p multiply-adds per point instead of 4 p.  One wavefront computes 16 rows k by 16 columns
-// (subsequences) in four accumulator tiles.  Their sums run in two halves: one chain of a composite
-// p rounds more than the short butterflies of its factors (FP64 application at 441 x 441: error
-// 5.3e-16 in one chain, 4.9e-16 in two, 4.9e-16 on the mixed-radix passes; 30.2 -> 30.5 us).  The
-// factors come from the length's own twiddle table in LDS (W_p^m = W_L^{q m}).  The direct sums this
-// replaces ran p^2 dependent table reads per subsequence on one thread.  FP64 application of
-// 201 x 151 x 101 points: 40.2 ms -> 0.406 ms, of 1023 x 767 points: 1.49 ms -> 0.057 ms; a CG body at
-// 85 x 85: 262 -> 32 us.
+// (subsequences) in four accumulator tiles.  Those of a composite p are summed in two chains (SPLIT,
+// even and odd steps): one rounds more than the short butterflies of its factors.  FP64 application
+// at 441 x 441: error 5.3e-16 in one chain, 4.9e-16 in two, 4.9e-16 on the mixed-radix passes.  For a
+// prime p one chain rounds less than the direct sums it replaces (511 x 509: 8.5e-16, 1.2e-15), and
+// two would be up to 5 % slower (89 x 89 FP32: 22.7 -> 23.8 us).  The factors come from the length's own
+// twiddle table in LDS (W_p^m = W_L^{q m}).  The direct sums ran p^2 dependent table reads per
+// subsequence on one thread.  FP64 application of 201 x 151 x 101 points: 40.2 ms -> 0.406 ms, of
+// 1023 x 767 points: 1.49 ms -> 0.057 ms; a CG body at 85 x 85: 262 -> 32 us.
 //
 // Every pass keeps its tile in one LDS buffer: a step whose outputs go to other slots than its
 // inputs came from holds the outputs in registers across a barrier (a thread has one step-A
@@ -29,6 +30,7 @@ namespace fgh {
 constexpr int kGenRadix = 17;       // largest register radix
 constexpr int kGenMaxThreads = 512;
 constexpr int kGenMaxItems = 4;     // products per wavefront
+constexpr int kGenSplit = 8;        // added to a kernel's NI: dense sums in two chains
 
 #define FGH_GEN_RADICES(X) X(1) X(3) X(5) X(7) X(9) X(11) X(13) X(15) X(17)
 
@@ -84,7 +86,7 @@ __device__ __forceinline__ void step_a_reg(const cpx<T>* src, cpx<T>* dst, int i
     lds_barrier();
 }
 
-template <typename T, bool INV, bool TW, int NI>
+template <typename T, bool INV, bool TW, int NI, bool SPLIT>
 __device__ __forceinline__ void step_a_dense(cpx<T>* X, const Lines& ln, int i1, int im, int o1, int ok, int q, int p,
                                              const cpx<T>* tw)
 {
@@ -116,44 +118,47 @@ __device__ __forceinline__ void step_a_dense(cpx<T>* X, const Lines& ln, int i1,
             w *= q;
             st *= q;
             int lo = g * is, hi = (p - g) * is;
-            auto mac = [&](cpx<T> f, cpx<T> a, cpx<T> b) {
-                acc[i][0] = Mfma<T>::mac(f.x, a.x, acc[i][0]);
-                acc[i][1] = Mfma<T>::mac(f.x, a.y, acc[i][1]);
-                acc[i][2] = Mfma<T>::mac(f.y, b.x, acc[i][2]);
-                acc[i][3] = Mfma<T>::mac(f.y, b.y, acc[i][3]);
+            auto mac = [&](V* s, cpx<T> f, cpx<T> a, cpx<T> b) {
+                s[0] = Mfma<T>::mac(f.x, a.x, s[0]);
+                s[1] = Mfma<T>::mac(f.x, a.y, s[1]);
+                s[2] = Mfma<T>::mac(f.y, b.x, s[2]);
+                s[3] = Mfma<T>::mac(f.y, b.y, s[3]);
                 w += st;
                 if (w >= L) w -= L;
                 lo += 4 * is;
                 hi -= 4 * is;
             };
-            auto steps = [&](int n) {
-#pragma unroll 2
-                for (int s = 0; s < n; s++) {
-                    const cpx<T> a = x[lo], b = x[hi];
-                    mac(tw[w], a + b, a - b);
-                }
+            auto step = [&](V* s) {
+                const cpx<T> a = x[lo], b = x[hi];
+                mac(s, tw[w], a + b, a - b);
             };
             const cpx<T> zero = {T(0), T(0)};
             {   // m = 0 has no mirror (its sine factor is 0)
                 const cpx<T> a = x[lo], b = g ? x[hi] : zero;
-                mac(tw[w], a + b, a - b);
+                mac(acc[i], tw[w], a + b, a - b);
             }
             const int full = (h + 1) >> 2;  // steps whose four m are all <= h
-            steps((full - 1) >> 1);
-            V half[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                half[u] = acc[i][u];
-                acc[i][u] = V{T(0), T(0), T(0), T(0)};
+            V odd[4] = {};
+            if constexpr (SPLIT) {
+                int s = 1;
+                for (; s + 1 < full; s += 2) {
+                    step(odd);
+                    step(acc[i]);
+                }
+                if (s < full) step(odd);
+            } else {
+#pragma unroll 2
+                for (int s = 1; s < full; s++) step(acc[i]);
             }
-            steps(full >> 1);
             if ((h + 1) & 3) {
                 const bool in = 4 * full + g <= h;
                 const cpx<T> a = in ? x[lo] : zero, b = in ? x[hi] : zero;
-                mac(tw[w], a + b, a - b);
+                mac(acc[i], tw[w], a + b, a - b);
             }
+            if constexpr (SPLIT) {
 #pragma unroll
-            for (int u = 0; u < 4; u++) acc[i][u] += half[u];
+                for (int u = 0; u < 4; u++) acc[i][u] += odd[u];
+            }
         }
     }
     lds_barrier();
@@ -191,7 +196,7 @@ __device__ __forceinline__ void step_a(cpx<T>* X, const Lines& ln, int i1, int i
 {
     const int q = ax.q, p = ax.p;
     if constexpr (NI > 0) {
-        step_a_dense<T, INV, TW, NI>(X, ln, i1, im, o1, ok, q, p, tw);
+        step_a_dense<T, INV, TW, (NI & 7), (NI & kGenSplit) != 0>(X, ln, i1, im, o1, ok, q, p, tw);
     } else {
         const int job = threadIdx.x;
         int n1, l;

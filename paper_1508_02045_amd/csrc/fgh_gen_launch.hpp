@@ -5,15 +5,18 @@
 
 namespace fgh {
 
-// NI: 0 (both steps in registers), 2 or 4 dense products per wavefront.
-#define FGH_GEN_NI(NI, CALL)                                \
-    switch (NI) {                                           \
-        case 0: return CALL(0);                             \
-        case 1:                                             \
-        case 2: return CALL(2);                             \
-        case 3:                                             \
-        case 4: return CALL(4);                             \
-    }                                                       \
+// Whether the dense step of a length is summed in two chains: p is no prime.
+inline bool split_sums(const Axis& ax) { return ax.rad[ax.nst - 1] != ax.p; }
+
+// NI: 0 (both steps in registers), 2 or 4 dense products per wavefront, plus kGenSplit.
+#define FGH_GEN_NI(NI, AX, CALL)                                             \
+    switch (NI) {                                                           \
+        case 0: return CALL(0);                                             \
+        case 1:                                                             \
+        case 2: return split_sums(AX) ? CALL(2 + kGenSplit) : CALL(2);      \
+        case 3:                                                             \
+        case 4: return split_sums(AX) ? CALL(4 + kGenSplit) : CALL(4);      \
+    }                                                                       \
     return hipErrorInvalidValue
 
 template <typename T, int D, int NI>
@@ -27,7 +30,7 @@ template <typename T>
 hipError_t gen_first(const OpPlan& op, const FirstArgs<T>& fa, int opc, unsigned nblk)
 {
 #define C(N) (op.g.d == 2 ? gen_first_ni<T, 2, N>(op, fa, opc, nblk) : gen_first_ni<T, 3, N>(op, fa, opc, nblk))
-    FGH_GEN_NI(op.ni_row, C);
+    FGH_GEN_NI(op.ni_row, fa.ax, C);
 #undef C
 }
 
@@ -42,7 +45,7 @@ template <typename T, int EPI>
 static hipError_t gen_last_epi(const OpPlan& op, const LastArgs<T>& la, unsigned nblk)
 {
 #define C(N) (op.g.d == 2 ? gen_last_ni<T, 2, EPI, N>(op, la, nblk) : gen_last_ni<T, 3, EPI, N>(op, la, nblk))
-    FGH_GEN_NI(op.ni_row, C);
+    FGH_GEN_NI(op.ni_row, la.ax, C);
 #undef C
 }
 
@@ -74,7 +77,7 @@ template <typename T, int EPI>
 static hipError_t gen_lastfirst_epi(const OpPlan& op, const LastArgs<T>& la, unsigned nblk)
 {
 #define C(N) (op.g.d == 2 ? gen_lastfirst_ni<T, 2, EPI, N>(op, la, nblk) : gen_lastfirst_ni<T, 3, EPI, N>(op, la, nblk))
-    FGH_GEN_NI(op.ni_row, C);
+    FGH_GEN_NI(op.ni_row, la.ax, C);
 #undef C
 }
 
@@ -107,7 +110,7 @@ template <typename T>
 hipError_t gen_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int B)
 {
 #define C(N) gen_axis_ni<T, N>(op, xa, inv, B)
-    FGH_GEN_NI(op.ni_axis, C);
+    FGH_GEN_NI(op.ni_axis, xa.ax, C);
 #undef C
 }
 
@@ -129,7 +132,7 @@ template <typename T>
 hipError_t gen_middle(const OpPlan& op, const MidArgs<T>& ma, int mult)
 {
 #define C(N) (op.g.d == 2 ? gen_middle_ni<T, 2, N>(op, ma, mult) : gen_middle_ni<T, 3, N>(op, ma, mult))
-    FGH_GEN_NI(op.ni_mid, C);
+    FGH_GEN_NI(op.ni_mid, ma.ax, C);
 #undef C
 }
 
