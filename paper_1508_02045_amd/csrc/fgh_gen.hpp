@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kGenMaxThreads) void kg_first(FirstArgs<T> a, int o
         for (int base = 0; base < total; base += KU * blockDim.x)
             first_stage0_chunk<T, D, 0, KU>(a, op, tab, beta, base, total, lim, row0 * L, Zr, rl, L, acc);
     }
-    if (sizeof(T) == 8 && a.pq_part) {
+    if (sizeof(T) == 8 && op == OP_AP_CG && a.pq_part) {
         const double tot = block_sum(acc, red);
         if (threadIdx.x == 0) a.pq_part[blockIdx.x] = tot;
     }
@@ -515,7 +515,7 @@ template <typename T, bool INV, int NI>
 __global__ __launch_bounds__(kGenMaxThreads) void kg_axis(AxisArgs<T> a, int B)
 {
     int b = blockIdx.x;
-    if (!INV && a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
+    if (!INV && a.pending && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, P = a.P, q = a.ax.q, p = a.ax.p;
@@ -702,7 +702,7 @@ template <typename T, int D, int MULT, int NI>
 __global__ __launch_bounds__(kGenMaxThreads) void kg_middle(MidArgs<T> a)
 {
     int b = blockIdx.x;
-    if (D == 2 && a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
+    if (D == 2 && a.pending && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, P = a.P, q = a.ax.q, p = a.ax.p, NS = 2 * P;

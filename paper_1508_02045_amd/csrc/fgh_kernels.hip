@@ -129,7 +129,7 @@ template <typename T, bool INV>
 __global__ __launch_bounds__(kThreads) void k_axis(AxisArgs<T> a)
 {
     int b = blockIdx.x;
-    if (!INV && a.pend.sc && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
+    if (!INV && a.pending && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L;
@@ -177,7 +177,7 @@ template <typename T, int D, int MULT>
 __global__ __launch_bounds__(kThreads) void k_middle(MidArgs<T> a)
 {
     int tile = blockIdx.x;
-    if (D == 2 && a.pend.sc && (tile -= Pending::kBlocks) < 0)
+    if (D == 2 && a.pending && (tile -= Pending::kBlocks) < 0)
         return finish_pending(a.pend, tile + Pending::kBlocks);
     if (a.done && *a.done) return;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1362,6 +1362,7 @@ static MidArgs<T> mid_args(const OpPlan& op, cpx<T>* buf, const int* done)
     ma.twg = static_cast<const cpx<T>*>(op.tw[0]);
     ma.done = done;
     ma.pend = Pending{};
+    ma.pending = 0;
     return ma;
 }
 
@@ -1433,6 +1434,7 @@ static hipError_t build_bundle_d(const OpPlan& op, const ApplyArgs& a, ApplyBund
         xa.outer = g.L[0];
         xa.comps = D;
         xa.pend = pend;
+        xa.pending = pend.blocks();
         mid = SB;
         AxisArgs<T>& xi = bu->xi;
         xi.ax = op.ax[1];
@@ -1455,7 +1457,10 @@ static hipError_t build_bundle_d(const OpPlan& op, const ApplyArgs& a, ApplyBund
         xi.comps = D;
     }
     bu->ma = mid_args<T>(op, mid, done);
-    if (D == 2) bu->ma.pend = pend;
+    if (D == 2) {
+        bu->ma.pend = pend;
+        bu->ma.pending = pend.blocks();
+    }
 
     LastArgs<T>& la = bu->la;
     la.g = g;
