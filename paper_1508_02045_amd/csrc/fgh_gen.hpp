@@ -516,7 +516,7 @@ __global__ __launch_bounds__(kGenMaxThreads) void kg_axis(AxisArgs<T> a, int B)
 {
     int b = blockIdx.x;
     if (!INV && a.pending && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
-    if (a.done && *a.done) return;
+    if (stopped(a.done)) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, P = a.P, q = a.ax.q, p = a.ax.p;
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
@@ -703,7 +703,7 @@ __global__ __launch_bounds__(kGenMaxThreads) void kg_middle(MidArgs<T> a)
 {
     int b = blockIdx.x;
     if (D == 2 && a.pending && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
-    if (a.done && *a.done) return;
+    if (stopped(a.done)) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L, P = a.P, q = a.ax.q, p = a.ax.p, NS = 2 * P;
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kThreads) void k_axis(AxisArgs<T> a)
 {
     int b = blockIdx.x;
     if (!INV && a.pending && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
-    if (a.done && *a.done) return;
+    if (stopped(a.done)) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L;
     const int P = a.P;
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kThreads) void k_middle(MidArgs<T> a)
     int tile = blockIdx.x;
     if (D == 2 && a.pending && (tile -= Pending::kBlocks) < 0)
         return finish_pending(a.pend, tile + Pending::kBlocks);
-    if (a.done && *a.done) return;
+    if (stopped(a.done)) return;
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = a.ax.L;
     const int P = a.P;
@@ -1233,11 +1233,9 @@ static hipError_t v2_axis(const OpPlan& op, const AxisArgs<T>& xa, bool inv, int
 #define C(LL, A1, A2)                                                                        \
     case LL:                                                                                 \
         if (inv)                                                                             \
-            LAUNCH_LDS((k2_axis<T, A1, A2, true, false>), grid, lds, op.stream, xa, B);      \
-        else if (xa.pend.sc)                                                                 \
-            LAUNCH_LDS((k2_axis<T, A1, A2, false, true>), grid, lds, op.stream, xa, B);      \
+            LAUNCH_LDS((k2_axis<T, A1, A2, true>), grid, lds, op.stream, xa, B);             \
         else                                                                                 \
-            LAUNCH_LDS((k2_axis<T, A1, A2, false, false>), grid, lds, op.stream, xa, B);     \
+            LAUNCH_LDS((k2_axis<T, A1, A2, false>), grid, lds, op.stream, xa, B);            \
         break;
         V2_COL_CASES(C)
 #undef C
@@ -1322,7 +1320,7 @@ static hipError_t v2_middle_b(const OpPlan& op, const MidArgs<T>* tab, int mult,
 }
 
 template <typename T>
-static hipError_t v2_axis_b(const OpPlan& op, const AxisArgs<T>* tab, bool inv, bool pend, int blocks, int B, int nb)
+static hipError_t v2_axis_b(const OpPlan& op, const AxisArgs<T>* tab, bool inv, int blocks, int B, int nb)
 {
     const dim3 grid(blocks, nb);
     const size_t lds = op.lds_axis;
@@ -1330,11 +1328,9 @@ static hipError_t v2_axis_b(const OpPlan& op, const AxisArgs<T>* tab, bool inv, 
 #define C(LL, A1, A2)                                                                           \
     case LL:                                                                                    \
         if (inv)                                                                                \
-            LAUNCH_LDS((k2_axis_b<T, A1, A2, true, false>), grid, lds, op.stream, tab, B);      \
-        else if (pend)                                                                          \
-            LAUNCH_LDS((k2_axis_b<T, A1, A2, false, true>), grid, lds, op.stream, tab, B);      \
+            LAUNCH_LDS((k2_axis_b<T, A1, A2, true>), grid, lds, op.stream, tab, B);     \
         else                                                                                    \
-            LAUNCH_LDS((k2_axis_b<T, A1, A2, false, false>), grid, lds, op.stream, tab, B);     \
+            LAUNCH_LDS((k2_axis_b<T, A1, A2, false>), grid, lds, op.stream, tab, B);    \
         break;
         V2_COL_CASES(C)
 #undef C
@@ -1837,15 +1833,14 @@ static hipError_t apply_batch_d(const OpPlan& op, const ApplyBundle<T>& b0, cons
     hipError_t e;
     if (!b0.skip_first && (e = v2_first_b<T, D>(op, t.fa, b0.op, b0.nblk1, nb)) != hipSuccess) return e;
     if (b0.first_only) return hipSuccess;
-    if (D == 3 && (e = v2_axis_b<T>(op, t.xf, false, b0.xf.pend.sc, axis_blocks(b0.xf), g.B[1], nb)) != hipSuccess)
-        return e;
+    if (D == 3 && (e = v2_axis_b<T>(op, t.xf, false, axis_blocks(b0.xf), g.B[1], nb)) != hipSuccess) return e;
     const int mb = b0.ma.ntiles + b0.ma.pend.blocks();
     if constexpr (D == 2)
         e = b0.ma.pend.sc ? v2_middle_b<T, D, true>(op, t.ma, b0.mult, mb, nb) : v2_middle_b<T, D, false>(op, t.ma, b0.mult, mb, nb);
     else
         e = v2_middle_b<T, D, false>(op, t.ma, b0.mult, mb, nb);
     if (e != hipSuccess) return e;
-    if (D == 3 && (e = v2_axis_b<T>(op, t.xi, true, false, axis_blocks(b0.xi), g.B[1], nb)) != hipSuccess) return e;
+    if (D == 3 && (e = v2_axis_b<T>(op, t.xi, true, axis_blocks(b0.xi), g.B[1], nb)) != hipSuccess) return e;
     return v2_last_b<T, D>(op, t.la, b0.epi, b0.fused, b0.nblk_last, nb);
 }
 

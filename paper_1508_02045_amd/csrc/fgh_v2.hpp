@@ -33,6 +33,14 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The loop's stop flag, for the passes that may run beside the workgroup that sets it (Pending).  A
+// relaxed atomic, and so a vector load: a scalar load in every workgroup cost 1 % of the strided
+// passes (243^3 FP64 141.2 -> 142.6 us, a CG body 1111 -> 1116 us).
+__device__ __forceinline__ bool stopped(const int* done)
+{
+    return done && __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // What ends a loop whose stopping-test value (raw sum) is v after its next body: 0 nothing, else
 // Scalars::done.
 __device__ __forceinline__ int end_state(const Scalars* s, double v)
@@ -872,9 +880,16 @@ __device__ __forceinline__ void first_body(const FirstArgs<T>& a, int op, int b,
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* Zc = tw + L;
     T* tab = reinterpret_cast<T*>(Zc + npairs * L);
-    for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
+    // in two parts for CG (1 us of 415 at 243^3 FP64); a plain pass on a small grid waits for the loads
+    // that the other lanes make there (63^2 FP32 application 14.95 -> 14.79 us with one part)
+    TwiddleCopy<T, L> tc;
+    if (CG)
+        tc.load(a.twg);
+    else
+        for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = a.twg[m];
     if (a.A.kind == AK_PHASE)
         for (int m = threadIdx.x; m < kMaxPhases * 6; m += blockDim.x) tab[m] = T(a.A.tab[m / 6][m % 6]);
+    if (CG) tc.store(tw);
     if ((a.rpb * D) & 1)  // the imaginary half of the last packed row is a zero row
         for (int i = threadIdx.x; i < L; i += blockDim.x) Zc[(npairs - 1) * L + i].y = T(0);
     T beta = T(0);
@@ -951,12 +966,12 @@ __device__ __forceinline__ void run_jobs(int n, FT table, FL load_transform, FX 
 // Strided axis pass (3D axis 1), one component per workgroup, tile of P columns.
 // ------------------------------------------------------------------------------------------
 // b: the workgroup's linear id over the (tile, outer, component) grid of one plan, after that of the
-// pending loop reductions (PEND: a.pend.sc is set; a kernel of its own, see first_body).
-template <typename T, int L1, int L2, bool INV, bool PEND>
+// pending loop reductions (forward passes).
+template <typename T, int L1, int L2, bool INV>
 __device__ __forceinline__ void axis_body(const AxisArgs<T>& a, int B, int b)
 {
-    if (PEND && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
-    if (a.done && *a.done) return;
+    if (!INV && a.pending && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
+    if (stopped(a.done)) return;
     const int gx = a.ntiles, gy = a.outer;
     constexpr int L = L1 * L2;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1025,17 +1040,17 @@ __device__ __forceinline__ void axis_body(const AxisArgs<T>& a, int B, int b)
     }
 }
 
-template <typename T, int L1, int L2, bool INV, bool PEND>
+template <typename T, int L1, int L2, bool INV>
 __global__ __launch_bounds__(kThreads) void k2_axis(AxisArgs<T> a, int B)
 {
-    axis_body<T, L1, L2, INV, PEND>(a, B, blockIdx.x);
+    axis_body<T, L1, L2, INV>(a, B, blockIdx.x);
 }
 
 // Several plans of one shape: member blockIdx.y.
-template <typename T, int L1, int L2, bool INV, bool PEND>
+template <typename T, int L1, int L2, bool INV>
 __global__ __launch_bounds__(kThreads) void k2_axis_b(const AxisArgs<T>* __restrict__ tab, int B)
 {
-    axis_body<T, L1, L2, INV, PEND>(tab[blockIdx.y], B, blockIdx.x);
+    axis_body<T, L1, L2, INV>(tab[blockIdx.y], B, blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1046,7 +1061,7 @@ template <typename T, int D, int L1, int L2, int MULT, bool PEND>
 __device__ __forceinline__ void middle_body(const MidArgs<T>& a, int b)
 {
     if (PEND && (b -= Pending::kBlocks) < 0) return finish_pending(a.pend, b + Pending::kBlocks);
-    if (a.done && *a.done) return;
+    if (stopped(a.done)) return;
     constexpr int L = L1 * L2;
     extern __shared__ __align__(16) unsigned char smem[];
     cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem);
